@@ -197,15 +197,15 @@ size_t cached_workspace_bytes(int dev) {
   return bytes;
 }
 
-// Workgroups of the statistics kernel one compute unit holds at once, per
-// device, storage type and head dimensions (cached; 0 = not yet known).
-int stats_blocks_per_cu(int dev, bool is_f32, int d_k, int d_v) {
-  static std::atomic<int> cache[kMaxDevices][2][3][3];
+// Workgroups of the bf16 statistics kernel one compute unit holds at once,
+// per device and head dimensions (cached; 0 = not yet known).
+int stats_blocks_per_cu(int dev, int d_k, int d_v) {
+  static std::atomic<int> cache[kMaxDevices][3][3];
   auto idx = [](int d) { return d == 32 ? 0 : d == 64 ? 1 : 2; };
-  std::atomic<int>& c = cache[dev][is_f32 ? 1 : 0][idx(d_k)][idx(d_v)];
+  std::atomic<int>& c = cache[dev][idx(d_k)][idx(d_v)];
   int n = c.load(std::memory_order_relaxed);
   if (n == 0) {
-    n = vda::stats_blocks_per_cu(is_f32, d_k, d_v);
+    n = vda::stats_blocks_per_cu(d_k, d_v);
     if (n < 1) n = 1;
     c.store(n, std::memory_order_relaxed);
   }
@@ -213,21 +213,29 @@ int stats_blocks_per_cu(int dev, bool is_f32, int d_k, int d_v) {
 }
 
 // Split plan of the statistics step.  Whole frames fill the device in
-// rounds of (resident workgroups) frames; when the last round is partial,
-// its frames are split into up to four token ranges (at least 256 tokens
-// each) so that the end of the launch keeps more compute units streaming.
-// Each extra range costs one partial A_t, B_t written here and read back by
-// the inverse step, which is why the split is kept small and limited to
-// the partial round.
+// rounds of `slots` frames; when the last round is partial, its frames are
+// split into token ranges so that the end of the launch keeps more compute
+// units busy.  Each extra range costs one partial A_t, B_t written here and
+// read back by the inverse step, which is why the split is kept small and
+// limited to the partial round.
+// bf16 storage: the step streams, so a round is every resident workgroup
+// (two per compute unit), and a range has at least 256 tokens, at most four
+// per frame.  fp32 storage: the step is bound by the fp32 matrix rate, which
+// the workgroups of a compute unit share, so a round is one frame per compute
+// unit (84 frames of 1560 tokens: 3 ranges, 252 workgroups; 4 ranges left
+// 80 compute units with two of 336); a token takes about 0.09 us of a compute
+// unit and a further partial about 1 us of the inverse, so up to eight
+// ranges of at least 128 tokens.
 vda::SplitPlan default_plan(int dev, int F, int N, int H, int d_k, int d_v, bool is_f32) {
-  constexpr int kMaxSplits = 4;
+  const int max_splits = is_f32 ? 8 : 4, min_tokens = is_f32 ? 128 : 256;
   const long long count = (long long)H * F;
-  const long long slots = (long long)stats_blocks_per_cu(dev, is_f32, d_k, d_v) * current_device_cus();
+  const long long slots =
+      (is_f32 ? 1LL : (long long)stats_blocks_per_cu(dev, d_k, d_v)) * current_device_cus();
   const long long rem = count % slots;
   if (rem == 0) return vda::SplitPlan{0, 1};
   long long k = slots / rem;
-  if (k > kMaxSplits) k = kMaxSplits;
-  if (k > N / 256) k = N / 256;
+  if (k > max_splits) k = max_splits;
+  if (k > N / min_tokens) k = N / min_tokens;
   if (k < 2) return vda::SplitPlan{0, 1};
   return vda::SplitPlan{(int)rem, (int)k};
 }

@@ -22,8 +22,8 @@ inline long long stats_workgroups(long long count, SplitPlan plan) {
   return plan.splits > 1 ? count - plan.tail + (long long)plan.tail * plan.splits : count;
 }
 
-// Statistics workgroups one compute unit holds at once (occupancy query).
-int stats_blocks_per_cu(bool is_f32, int d_k, int d_v);
+// bf16 statistics workgroups one compute unit holds at once (occupancy query).
+int stats_blocks_per_cu(int d_k, int d_v);
 
 // Step a1, Eq. 3b: partial frame statistics per token range.  lower_only
 // (bf16 storage): A_t's blocks above the diagonal are left unwritten, for a

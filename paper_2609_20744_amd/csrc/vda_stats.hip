@@ -97,6 +97,45 @@ struct WavePlan {
   static constexpr int imax = ncols == 2 ? (col(0) > col(1) ? col(0) : col(1)) : col(0);
 };
 
+// Stores wave W's blocks: A_t (the blocks above the diagonal too, unless
+// lower_only) and B_t.
+template <int DK, int DV, int W>
+__device__ __forceinline__ void store_stats_blocks(
+    const floatx4 (&accA)[WavePlan<DK / 16, DV / 16, W>::ncols][DK / 16],
+    const floatx4 (&accB)[DV / 16][WavePlan<DK / 16, DV / 16, W>::ncols], float* Ab, float* Bb,
+    bool lower_only, int li, int lg) {
+  using P = WavePlan<DK / 16, DV / 16, W>;
+  constexpr int NC = P::ncols;
+  // Block (rows rb, columns cb): lane holds rows 16 rb + 4 lg + e, column
+  // 16 cb + li.  The transposed copy of an off-diagonal A_t block puts the
+  // four rows of a lane into one 16-byte row piece.
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int j = P::col(c);
+    if (P::has_a) {
+#pragma unroll
+      for (int i = 0; i <= P::imax; ++i) {
+        if (i <= P::col(c)) {
+          // Block (j, i), on or below the diagonal, as the transpose of the
+          // accumulated block (i, j); the diagonal blocks too, so that the
+          // blocks the inverse reads are the same in both modes.
+          *reinterpret_cast<floatx4*>(&Ab[(j * 16 + li) * DK + i * 16 + lg * 4]) = accA[c][i];
+          if (!lower_only && i < P::col(c)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              Ab[(i * 16 + lg * 4 + e) * DK + j * 16 + li] = accA[c][i][e];
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int v = P::v_begin; v < P::v_end; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        Bb[(v * 16 + lg * 4 + e) * DK + j * 16 + li] = accB[v][c][e];
+  }
+}
+
 template <int DK, int DV>
 struct StatsFrame {
   static constexpr int LDK = tile_ld(DK);
@@ -210,34 +249,7 @@ struct StatsFrame {
     if (n_begin < n_end) load_tile(n_begin, kraw, kb, vraw);
     for (int n0 = n_begin; n0 < n_end; n0 += kStatsTile) tile_step(n0 + kStatsTile, kraw, kb, vraw);
 
-    // Block (rows rb, columns cb): lane holds rows 16 rb + 4 lg + e, column
-    // 16 cb + li.  The transposed copy of an off-diagonal A_t block puts the
-    // four rows of a lane into one 16-byte row piece.
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int j = P::col(c);
-      if (P::has_a) {
-#pragma unroll
-        for (int i = 0; i <= P::imax; ++i) {
-          if (i <= P::col(c)) {
-            // Block (j, i), on or below the diagonal, as the transpose of the
-            // accumulated block (i, j); the diagonal blocks too, so that the
-            // blocks the inverse reads are the same in both modes.
-            *reinterpret_cast<floatx4*>(&Ab[(j * 16 + li) * DK + i * 16 + lg * 4]) = accA[c][i];
-            if (!lower_only && i < P::col(c)) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                Ab[(i * 16 + lg * 4 + e) * DK + j * 16 + li] = accA[c][i][e];
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int v = P::v_begin; v < P::v_end; ++v)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          Bb[(v * 16 + lg * 4 + e) * DK + j * 16 + li] = accB[v][c][e];
-    }
+    store_stats_blocks<DK, DV, W>(accA, accB, Ab, Bb, lower_only, li, lg);
   }
 };
 
@@ -290,97 +302,210 @@ void stats_bf16_kernel(const uint16_t* __restrict__ K, const uint16_t* __restric
   }
 }
 
-// fp32 storage: plain fp32 products and sums (no rounding of beta * k).
-// The output X = [A_t; B_t] ((d_k + d_v) x d_k) is dealt out to the threads
-// in R x C register tiles (C = 8 columns, 4 for d_k = 32), so each token
-// costs a thread R + C LDS reads for R * C fused multiply-adds.  A tile of
-// 32 tokens of k, v and beta is loaded by range-checked buffer loads that
-// are all in flight together (tokens past the range read as zero), then
-// staged in LDS; every output sums its tokens in order.
+// fp32 storage: exact fp32 products (v_mfma_f32_16x16x4_f32; beta * k in
+// fp32) and sums, with the bf16 kernel's split of the output over the waves.
+// The contraction runs over tokens, four per product: lane (li, lg) supplies
+// token 4 s + lg of channel 16 i + li for both operands, which it reads as one
+// float of the natural-layout tile in LDS ([token][k, v channels], row
+// stride 16 mod 64 floats: the four tokens of a read lie on different banks).
+// beta * k is the k operand times the lane's token's beta, so no second
+// image of the keys is kept.  A tile is 16 tokens (32 for 32-channel heads),
+// the next one in flight in registers.  The sums run in two levels, 256
+// tokens in the products' accumulators and those into a second set of
+// registers: a single chain's rounding error grows with the tokens of the
+// range (whole pass against 64 bits at 4 heads x 21 frames x 1560 tokens,
+// 520 a range: 9.2e-7 with one chain, 8.2e-7 for ranges of 390).
+// What bounds it: the fp32 matrix rate (25 products of 32 cycles per wave
+// and four tokens at d = 128, A_t's upper triangle and B_t): 48 us of the
+// 75 us it takes at 4 heads x 21 frames x 1560 tokens x 128 channels; the
+// rest is the first tile, the stores and ~0.3 us per tile around its barrier.
+// On the vector ALUs, with every operand of a multiply-add read from LDS, it
+// took 316 us.  One wave per SIMD at d = 128 (the two sets of sums): with one
+// set, two waves and tiles of 16 tokens it took 84 us.
+constexpr int kF32Tile = 32;
+constexpr int kF32Chain = 256;  // tokens per accumulator chain
+
 template <int DK, int DV>
-__global__ __launch_bounds__(kThreads)
+struct StatsFrameF32 {
+  static constexpr int DX = DK + DV;
+  static constexpr int LD = ((DX + 63) / 64) * 64 + 16;
+  static constexpr int NKC = kF32Tile * (DK / 4) / kThreads;  // 16-byte K chunks per thread and tile
+  static constexpr int NVC = kF32Tile * (DV / 4) / kThreads;
+  static_assert(NKC * kThreads == kF32Tile * (DK / 4) && NVC * kThreads == kF32Tile * (DV / 4),
+                "chunks divide evenly");
+
+  float* xt;  // two tiles [token][k, v]  (LDS)
+  float* bt;  // two tiles [token] beta   (LDS)
+  __amdgpu_buffer_rsrc_t krsrc, vrsrc, brsrc;
+  int tid, li, lg;
+
+  __device__ void load_tile(int n0, u32x4 (&kr)[NKC], u32x4 (&vr)[NVC], float& b) const {
+#pragma unroll
+    for (int i = 0; i < NKC; ++i) {
+      const int c = tid + i * kThreads;
+      kr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                            krsrc, (int)((uint32_t)(n0 * (DK / 4) + c) * 16u), 0, 0));
+    }
+#pragma unroll
+    for (int i = 0; i < NVC; ++i) {
+      const int c = tid + i * kThreads;
+      vr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                            vrsrc, (int)((uint32_t)(n0 * (DV / 4) + c) * 16u), 0, 0));
+    }
+    b = load_f32(brsrc, (uint32_t)(n0 + tid % kF32Tile) * 4u);
+  }
+
+  __device__ void store_tile(int buf, const u32x4 (&kr)[NKC], const u32x4 (&vr)[NVC], float b) const {
+    u32x4* x4 = reinterpret_cast<u32x4*>(xt + buf * (kF32Tile * LD));
+#pragma unroll
+    for (int i = 0; i < NKC; ++i) {
+      const int c = tid + i * kThreads;
+      x4[(c / (DK / 4)) * (LD / 4) + c % (DK / 4)] = kr[i];
+    }
+#pragma unroll
+    for (int i = 0; i < NVC; ++i) {
+      const int c = tid + i * kThreads;
+      x4[(c / (DV / 4)) * (LD / 4) + DK / 4 + c % (DV / 4)] = vr[i];
+    }
+    if (tid < kF32Tile) bt[buf * kF32Tile + tid] = b;
+  }
+
+  // The whole token loop and the output stores of wave W.
+  template <int W>
+  __device__ void run(int n_begin, int n_end, float* Ab, float* Bb, bool lower_only) const {
+    using P = WavePlan<DK / 16, DV / 16, W>;
+    constexpr int NC = P::ncols;
+    floatx4 sumA[NC][DK / 16], sumB[DV / 16][NC];
+    floatx4 accA[NC][DK / 16], accB[DV / 16][NC];  // one chain's
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+#pragma unroll
+      for (int i = 0; i < DK / 16; ++i) sumA[c][i] = accA[c][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int v = 0; v < DV / 16; ++v) sumB[v][c] = accB[v][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    u32x4 kr[NKC], vr[NVC];
+    float b;
+    // Two tiles in LDS: while one is multiplied, the next (loaded during the
+    // step before) is stored to the other and the one after it is loaded, so
+    // a step has one barrier.  Rows past n_end read as zero; the tiles past
+    // the range are never multiplied.
+    load_tile(n_begin, kr, vr, b);
+    store_tile(0, kr, vr, b);
+    load_tile(n_begin + kF32Tile, kr, vr, b);
+    int buf = 0;
+    for (int m0 = n_begin; m0 < n_end; m0 += kF32Chain) {
+      const int m1 = min(n_end, m0 + kF32Chain);
+      for (int n0 = m0; n0 < m1; n0 += kF32Tile, buf ^= 1) {
+        lds_barrier();  // this tile is complete; the other's operand reads are done
+        store_tile(buf ^ 1, kr, vr, b);
+        load_tile(n0 + 2 * kF32Tile, kr, vr, b);
+        const float* xb = xt + buf * (kF32Tile * LD);
+        const float* bb = bt + buf * kF32Tile;
+        // Operands of four tokens: rows of k and v, and beta.  The next four
+        // tokens' are read (pinned before the products, which the scheduler
+        // would otherwise make wait for each read) while these are multiplied.
+        constexpr int NA = P::has_a ? P::imax + 1 : 0, NV = P::v_end - P::v_begin;
+        float ka[2][NA > 0 ? NA : 1], kc[2][NC], va[2][NV], be[2];
+        auto read_ops = [&](int s) {
+          const float* row = xb + (4 * s + lg) * LD + li;
+          be[s & 1] = bb[4 * s + lg];
+#pragma unroll
+          for (int i = 0; i < NA; ++i) ka[s & 1][i] = row[i * 16];
+          if constexpr (NA == 0) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) kc[s & 1][c] = row[P::col(c) * 16];
+          }
+#pragma unroll
+          for (int v = 0; v < NV; ++v) va[s & 1][v] = row[DK + (P::v_begin + v) * 16];
+        };
+        read_ops(0);
+#pragma unroll
+        for (int s = 0; s < kF32Tile / 4; ++s) {
+          if (s + 1 < kF32Tile / 4) read_ops(s + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          float bop[NC];
+#pragma unroll
+          for (int c = 0; c < NC; ++c)
+            bop[c] = (NA > 0 ? ka[s & 1][NA > 0 ? P::col(c) : 0] : kc[s & 1][c]) * be[s & 1];
+#pragma unroll
+          for (int v = 0; v < NV; ++v)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              accB[P::v_begin + v][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                  va[s & 1][v], bop[c], accB[P::v_begin + v][c], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              if (i <= P::col(c))
+                accA[c][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[s & 1][i], bop[c], accA[c][i], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (P::has_a) {
+#pragma unroll
+          for (int i = 0; i <= P::col(c); ++i) {
+            sumA[c][i] += accA[c][i];
+            accA[c][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+        }
+#pragma unroll
+        for (int v = P::v_begin; v < P::v_end; ++v) {
+          sumB[v][c] += accB[v][c];
+          accB[v][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+    }
+    store_stats_blocks<DK, DV, W>(sumA, sumB, Ab, Bb, lower_only, li, lg);
+  }
+};
+
+template <int DK, int DV>
+__global__ __launch_bounds__(kThreads, 1)
 void stats_f32_kernel(const float* __restrict__ K, const float* __restrict__ V,
                       const float* __restrict__ beta, int N, int tokens_per_split,
                       unsigned tail, int splits, unsigned fh_count,
-                      float* __restrict__ A_part, float* __restrict__ B_part) {
-  constexpr int DX = DK + DV;
-  constexpr int T = 32;
-  constexpr int C = DK >= 64 ? 8 : 4;          // columns per thread
-  constexpr int CG = DK / C;                   // column groups
-  constexpr int R = DX * CG / kThreads;        // rows per thread
-  static_assert(R * C * kThreads == DX * DK, "register tiles cover the output");
-  constexpr int LPT = T * DX / kThreads;       // loaded elements per thread and tile
-  static_assert(LPT * kThreads == T * DX, "tile loads divide evenly");
-  __shared__ __align__(16) float xs[T][DX];
-  __shared__ __align__(16) float ys[T][DK];
+                      float* __restrict__ A_part, float* __restrict__ B_part, int lower_only) {
+  using S = StatsFrameF32<DK, DV>;
+  __shared__ __align__(16) float xt[2 * kF32Tile * S::LD];
+  __shared__ float bt[2 * kF32Tile];
 
   const StatsItem it = stats_item(blockIdx.x, fh_count, tail, splits, N, tokens_per_split);
   const unsigned fh = (unsigned)uniform((int)it.fh);
+  const unsigned slot = (unsigned)uniform((int)it.slot);
   const int n_begin = uniform(it.n_begin);
   const int n_end = uniform(it.n_end);
   const int tid = threadIdx.x;
-  const __amdgpu_buffer_rsrc_t krsrc = make_rsrc(K + (size_t)fh * N * DK, (uint32_t)(n_end * DK * 4));
-  const __amdgpu_buffer_rsrc_t vrsrc = make_rsrc(V + (size_t)fh * N * DV, (uint32_t)(n_end * DV * 4));
-  const __amdgpu_buffer_rsrc_t brsrc = make_rsrc(beta + (size_t)fh * N, (uint32_t)(n_end * 4));
-  const int j0 = (tid % CG) * C;
-  const int x0 = (tid / CG) * R;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (scalar)
 
-  float acc[R][C];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc[r][c] = 0.f;
+  S s;
+  s.xt = xt;
+  s.bt = bt;
+  s.krsrc = make_rsrc(K + (size_t)fh * N * DK, (uint32_t)(n_end * DK * 4));
+  s.vrsrc = make_rsrc(V + (size_t)fh * N * DV, (uint32_t)(n_end * DV * 4));
+  s.brsrc = make_rsrc(beta + (size_t)fh * N, (uint32_t)(n_end * 4));
+  s.tid = tid;
+  s.li = lane & 15;
+  s.lg = lane >> 4;
 
-  for (int n0 = n_begin; n0 < n_end; n0 += T) {
-    float xv[LPT], bv[LPT];
-#pragma unroll
-    for (int l = 0; l < LPT; ++l) {
-      const int idx = tid + l * kThreads;
-      const int e = idx / DX, c = idx % DX;
-      const uint32_t n = (uint32_t)(n0 + e);
-      xv[l] = c < DK ? load_f32(krsrc, (n * DK + c) * 4u) : load_f32(vrsrc, (n * DV + c - DK) * 4u);
-      bv[l] = load_f32(brsrc, n * 4u);
-    }
-    lds_barrier();  // the previous tile's reads are done
-#pragma unroll
-    for (int l = 0; l < LPT; ++l) {
-      const int idx = tid + l * kThreads;
-      const int e = idx / DX, c = idx % DX;
-      xs[e][c] = xv[l];
-      if (c < DK) ys[e][c] = xv[l] * bv[l];
-    }
-    lds_barrier();
-#pragma unroll 4
-    for (int e = 0; e < T; ++e) {
-      float xr[R], yc[C];
-#pragma unroll
-      for (int r = 0; r < R; ++r) xr[r] = xs[e][x0 + r];
-#pragma unroll
-      for (int c = 0; c < C; ++c) yc[c] = ys[e][j0 + c];
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int c = 0; c < C; ++c) acc[r][c] = fmaf(xr[r], yc[c], acc[r][c]);
-    }
-  }
-  float* Ab = A_part + (size_t)it.slot * (DK * DK);
-  float* Bb = B_part + (size_t)it.slot * (DV * DK);
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int x = x0 + r;
-    float* dst = x < DK ? Ab + (size_t)x * DK + j0 : Bb + (size_t)(x - DK) * DK + j0;
-#pragma unroll
-    for (int c = 0; c < C; c += 4)
-      *reinterpret_cast<float4*>(dst + c) = make_float4(acc[r][c], acc[r][c + 1], acc[r][c + 2],
-                                                        acc[r][c + 3]);
+  float* Ab = A_part + (size_t)slot * (DK * DK);
+  float* Bb = B_part + (size_t)slot * (DV * DK);
+  // Every branch runs the same number of barriers.
+  switch (wave) {
+    case 0: s.template run<0>(n_begin, n_end, Ab, Bb, lower_only != 0); break;
+    case 1: s.template run<1>(n_begin, n_end, Ab, Bb, lower_only != 0); break;
+    case 2: s.template run<2>(n_begin, n_end, Ab, Bb, lower_only != 0); break;
+    default: s.template run<3>(n_begin, n_end, Ab, Bb, lower_only != 0); break;
   }
 }
 
 template <int DK, int DV>
-int blocks_per_cu_t(bool is_f32) {
+int blocks_per_cu_t() {
   int n = 0;
-  const void* fn = is_f32 ? reinterpret_cast<const void*>(&stats_f32_kernel<DK, DV>)
-                          : reinterpret_cast<const void*>(&stats_bf16_kernel<DK, DV>);
+  const void* fn = reinterpret_cast<const void*>(&stats_bf16_kernel<DK, DV>);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kThreads, 0) != hipSuccess) return 1;
   return n;
 }
@@ -397,7 +522,7 @@ hipError_t launch_stats_t(bool is_f32, const void* k, const void* v, const float
   if (is_f32) {
     hipLaunchKernelGGL((stats_f32_kernel<DK, DV>), grid, dim3(kThreads), 0, stream,
                        static_cast<const float*>(k), static_cast<const float*>(v), beta, N, tps,
-                       tail, splits, fh_count, A_part, B_part);
+                       tail, splits, fh_count, A_part, B_part, (int)lower_only);
   } else {
     hipLaunchKernelGGL((stats_bf16_kernel<DK, DV>), grid, dim3(kThreads), 0, stream,
                        static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), beta, N,
@@ -408,9 +533,9 @@ hipError_t launch_stats_t(bool is_f32, const void* k, const void* v, const float
 
 }  // namespace
 
-int stats_blocks_per_cu(bool is_f32, int d_k, int d_v) {
+int stats_blocks_per_cu(int d_k, int d_v) {
 #define VDA_OCC_CASE(DKV, DVV) \
-  if (d_k == DKV && d_v == DVV) return blocks_per_cu_t<DKV, DVV>(is_f32);
+  if (d_k == DKV && d_v == DVV) return blocks_per_cu_t<DKV, DVV>();
   VDA_OCC_CASE(32, 32) VDA_OCC_CASE(32, 64) VDA_OCC_CASE(32, 128)
   VDA_OCC_CASE(64, 32) VDA_OCC_CASE(64, 64) VDA_OCC_CASE(64, 128)
   VDA_OCC_CASE(128, 32) VDA_OCC_CASE(128, 64) VDA_OCC_CASE(128, 128)

@@ -1,0 +1,64 @@
+"""The fp32 storage path's kernels at the edges of their tiles, against fp64 on the CPU, each within the bound that
+its own rounding gives: u = 2^-24 per operation of the longest chain of sums, over the sum of the terms' magnitudes.
+"""
+import numpy as np
+import pytest
+
+import oracle.vda_oracle as O
+from vda_testutil import fold_partials, to_device
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def V():
+    import torch
+    assert torch.cuda.is_available(), "the gpu tests need an MI355X"
+    from paper_2609_20744_amd import vda
+    return vda
+
+
+# Tokens: one, around the tile (32) and the accumulator chain (256) of a range, and ranges of every remainder.
+@pytest.mark.parametrize("N,tail,splits", [(1, 0, 1), (31, 0, 1), (32, 0, 1), (33, 0, 1), (255, 0, 1), (257, 0, 1),
+                                           (520, 2, 2), (1025, 1, 8)])
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 32), (32, 128), (128, 64)])
+def test_stats(V, N, tail, splits, dk, dv):
+    rng = np.random.default_rng(N + dk + dv)
+    k, v = (rng.standard_normal((1, 3, N, d)).astype(np.float32) for d in (dk, dv))
+    beta = rng.random((1, 3, N)).astype(np.float32)
+    beta[:, :, ::7] = 0.0
+    A, B = V.frame_stats(to_device(k, "f32"), to_device(v, "f32"), to_device(beta, "f32"), splits=splits,
+                         tail_frames=tail)
+    A = fold_partials(A.double(), 3, tail, splits).cpu().numpy()
+    B = fold_partials(B.double(), 3, tail, splits).cpu().numpy()
+    # beta * k, 256 sums in a chain, the chains' sums, and one spare.
+    rel = U * (1 + min(N, 256) + -(-N // 256) + 1)
+    for t in range(3):
+        As, Bs = O.frame_statistics(*(x[0, t].astype(np.float64) for x in (k, v, beta)))
+        Aa, Ba = O.frame_statistics(*(np.abs(x[0, t]).astype(np.float64) for x in (k, v, beta)))
+        assert np.all(np.abs(A[t] - As) <= rel * Aa)
+        assert np.all(np.abs(B[t] - Bs) <= rel * Ba)
+
+
+# Tokens: one, around a wave's 16, a step's 64, and workgroups with and without a last step.
+@pytest.mark.parametrize("H,N", [(1, 1), (2, 15), (1, 17), (2, 64), (1, 65), (3, 129), (70, 200)])
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 32), (32, 128), (128, 64)])
+def test_readout(V, H, N, dk, dv):
+    F = 2
+    rng = np.random.default_rng(N + dk + dv)
+    q = rng.standard_normal((H, F, N, dk)).astype(np.float32)
+    sf, sr = (rng.standard_normal((H, F, dv, dk)).astype(np.float32) for _ in range(2))
+    gate = rng.random(H).astype(np.float32)
+    y = V.readout(*(to_device(x, "f32") for x in (q, sf, sr, gate))).double().cpu().numpy()
+    S = sf.astype(np.float64) + sr
+    o = np.einsum("hftk,hfvk->hftv", q.astype(np.float64), S)
+    # S~'s sum and the d_k products' chain.
+    do = U * (dk + 2) * np.einsum("hftk,hfvk->hftv", np.abs(q).astype(np.float64), np.abs(S))
+    rms = np.sqrt((o * o).mean(-1, keepdims=True) + 1e-6)
+    g = gate.astype(np.float64)[:, None, None, None]
+    ref = g * o / rms
+    # The norm's own sum of d_v squares (relative error U * d_v / 2), root, quotient and product.
+    bound = g / rms * (do + np.abs(o) / rms * do.max(-1, keepdims=True)) + U * (dv / 2 + 8) * np.abs(ref)
+    assert np.all(np.abs(y - ref) <= bound)
