@@ -278,85 +278,151 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
   }
 }
 
-// fp32 storage: fp32 products and sums.  16 threads per token, each owning
-// d_v/16 output channels; S~ in LDS (fp32), queries staged per 16 tokens.
+// fp32 storage: exact fp32 products (v_mfma_f32_16x16x4_f32) and sums, laid
+// out as the bf16 path: O^T = S~ Q^T with S~ as the A-operand and the
+// queries of one 16-token group per wave as the B-operand.  Lane group lg of
+// k chunk c supplies the channels 16 c + 4 lg + s (s = 0..3, one product
+// each), so both operands are 16-byte pieces: the queries straight from
+// memory (one step's loads in flight during the previous one's products),
+// S~ from its fp32 image in LDS (row stride DK + 4 floats: the 16 rows of
+// a lane group start on different banks).
+// What bounds it: the fp32 matrix rate (2 d_k d_v flop per token, 32 cycles
+// per product); the LDS reads of S~ take a quarter of the LDS rate meanwhile.
+// 57 us at 4 heads x 21 frames x 1560 tokens x 128 channels (33 us of
+// products on the busiest compute unit; 344 us on the vector ALUs with an LDS
+// read per multiply-add); two 16-token groups per wave and step 71 us (a
+// coarser split of the frames).
 template <int DK, int DV, bool TOKGATE>
-__global__ __launch_bounds__(kThreads)
+__global__ __launch_bounds__(kThreads, 2)
 void readout_f32_kernel(const float* __restrict__ Q, const float* __restrict__ S_fwd,
                         const float* __restrict__ S_rev, const float* __restrict__ gate,
-                        int F, int N, int chunks, int tokens_per_chunk, int dvo, int oh, int qh,
+                        int F, int N, int chunks, unsigned nwg, int dvo, int oh, int qh,
                         int ql2, const float* __restrict__ alpha, int wchunk, int wradius,
                         int woffset, const float* __restrict__ gtok, float* __restrict__ out) {
-  constexpr int SLD = DK + 1;
-  constexpr int VPT = DV / 16;  // output channels per thread
-  __shared__ float st[DV * SLD];
-  __shared__ float qs[16][DK];
+  constexpr int SLD = DK + 4;  // fp32 row stride of S~ in LDS
+  constexpr int MB = DV / 16;  // 16-row blocks of S~ (output channels)
+  constexpr int KC = DK / 16;  // 16-channel k chunks
+  __shared__ __align__(16) float st[DV * SLD];
 
-  const unsigned fh = blockIdx.x / chunks;
-  const int chunk = blockIdx.x % chunks;
-  const int n_begin = chunk * tokens_per_chunk;
-  const int n_end = min(N, n_begin + tokens_per_chunk);
+  // The workgroups of one frame read the same two states: keep them on one XCD.
+  const unsigned L = xcd_grouped_id(blockIdx.x, nwg);
+  const unsigned fh = L / (unsigned)chunks;
+  const int chunk = (int)(L % (unsigned)chunks);
   const float g = TOKGATE ? 1.0f : gate[fh / F];
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (scalar)
+  const int li = lane & 15;
+  const int lg = lane >> 4;
   const float inv_norm = 1.0f / (float)dvo;
   // Query and output rows as in readout_bf16_kernel.
-  const size_t qrs = (size_t)qh * DK;
-  const float* qbase = Q + (((size_t)(fh / F / qh) * F + fh % F) * N * qh + (fh / F) % qh) * DK;
-  const size_t ors = (size_t)oh * dvo;
-  float* obase = out + (((size_t)(fh / F / oh) * F + fh % F) * N * oh + (fh / F) % oh) * dvo;
+  const unsigned hp = fh / F, fr = fh % F;
+  const uint32_t qrs = (uint32_t)qh * DK;
+  const float* qbase = Q + (((size_t)(hp / (unsigned)qh) * F + fr) * N * qh + hp % (unsigned)qh) * DK;
+  const uint32_t ors = (uint32_t)oh * (uint32_t)dvo;
+  float* obase = out + (((size_t)(hp / (unsigned)oh) * F + fr) * N * oh + hp % (unsigned)oh) * dvo;
 
-  // Gather (Eq. A.4), as in readout_bf16_kernel.
-  const int h = (int)(fh / F), f = (int)(fh % F);
-  const Window w = local_window(f, F, wchunk, wradius, woffset);
-  const float* sf = S_fwd + ((size_t)h * F + w.lo) * (DV * DK);
-  const float* sr = S_rev + ((size_t)h * F + w.hi) * (DV * DK);
-  static_assert(kThreads % DK == 0, "fixed column per thread");
-  float df[1], dr[1];
-  bridge_decay<1>(alpha, h, F, DK, tid % DK, f, w, df, dr);
-  for (int idx = tid; idx < DV * DK; idx += kThreads)
-    st[(idx / DK) * SLD + idx % DK] = sf[idx] * df[0] + sr[idx] * dr[0];
+  // The frame's 64-token super-groups are dealt out to its workgroups in
+  // turn, as in readout_bf16_kernel; rows past the frame are clamped onto its
+  // last row, and their outputs dropped by the range-checked stores.
+  const int n_first = chunk * 64 + wave * 16;
+  const int S = 64 * chunks;
+  floatx4 qn[KC];
+  auto load_q = [&](int n0) {
+    const int row = min(n0 + li, N - 1);
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+      qn[c] = *reinterpret_cast<const floatx4*>(qbase + (size_t)row * qrs + 16 * c + 4 * lg);
+  };
+  load_q(n_first);
 
-  const int tok = tid >> 4;  // token within the group of 16
-  const int part = tid & 15;
-  for (int n0 = n_begin; n0 < n_end; n0 += 16) {
-    lds_barrier();
-    for (int idx = tid; idx < 16 * DK; idx += kThreads) {
-      const int e = idx / DK, c = idx % DK;
-      const int n = n0 + e;
-      qs[e][c] = n < n_end ? qbase[(size_t)n * qrs + c] : 0.f;
-    }
-    lds_barrier();
-    float o[VPT];
+  {
+    // Gather (Eq. A.4), as in readout_bf16_kernel.
+    const int h = (int)hp, f = (int)fr;
+    const Window w = local_window(f, F, wchunk, wradius, woffset);
+    const float* sf = S_fwd + ((size_t)h * F + w.lo) * (DV * DK);
+    const float* sr = S_rev + ((size_t)h * F + w.hi) * (DV * DK);
+    float df[4], dr[4];
+    bridge_decay<4>(alpha, h, F, DK, (tid * 4) % DK, f, w, df, dr);
 #pragma unroll
-    for (int m = 0; m < VPT; ++m) o[m] = 0.f;
-    for (int c = 0; c < DK; ++c) {
-      const float qv = qs[tok][c];
-#pragma unroll
-      for (int m = 0; m < VPT; ++m) o[m] = fmaf(st[(part + 16 * m) * SLD + c], qv, o[m]);
+    for (int it = 0; it < (DV * DK) / (kThreads * 4); ++it) {
+      const int idx = tid * 4 + it * (kThreads * 4);
+      const float4 a = *reinterpret_cast<const float4*>(sf + idx);
+      const float4 b = *reinterpret_cast<const float4*>(sr + idx);
+      reinterpret_cast<floatx4*>(st)[((idx / DK) * SLD + idx % DK) / 4] =
+          floatx4{a.x * df[0] + b.x * dr[0], a.y * df[1] + b.y * dr[1], a.z * df[2] + b.z * dr[2],
+                  a.w * df[3] + b.w * dr[3]};
     }
+  }
+  lds_barrier();
+
+  const __amdgpu_buffer_rsrc_t grsrc =
+      make_rsrc(TOKGATE ? gtok + (size_t)fh * N * DV : Q, TOKGATE ? (uint32_t)N * DV * 4u : 0u);
+  const __amdgpu_buffer_rsrc_t orsrc =
+      make_rsrc(obase, ((uint32_t)(N - 1) * ors + (uint32_t)dvo) * 4u);
+  const floatx4* st4 = reinterpret_cast<const floatx4*>(st) + (li * SLD + 4 * lg) / 4;
+
+  for (int n0 = n_first; n0 < N; n0 += S) {
+    floatx4 qv[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) qv[c] = qn[c];
+    load_q(n0 + S);
+    // (An opaque zero offset keeps the compiler from hoisting the LDS operand
+    // reads out of the loop into registers.)
+    int zero_off;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero_off));
+    floatx4 acc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // The next chunk's S~ is read during the current one's products.
+    floatx4 a[2][MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) a[0][mb] = st4[zero_off + mb * 4 * SLD];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      if (c + 1 < KC) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) a[(c + 1) & 1][mb] = st4[zero_off + mb * 4 * SLD + 4 * (c + 1)];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c & 1][mb][s], qv[c][s], acc[mb], 0, 0, 0);
+    }
+    // lane holds o[token n][mb*16 + 4*lg + i]
+    const int n = n0 + li;
     float ss = 0.f;
 #pragma unroll
-    for (int m = 0; m < VPT; ++m) ss = fmaf(o[m], o[m], ss);
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
+      for (int i = 0; i < 4; ++i) ss = fmaf(acc[mb][i], acc[mb][i], ss);
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
     // A raw query, as in readout_bf16_kernel: |q|^2 over the token's row.
     float qn2 = 1.0f;
     if (ql2) {
       float s = 0.f;
-      for (int c = part; c < DK; c += 16) s = fmaf(qs[tok][c], qs[tok][c], s);
 #pragma unroll
-      for (int off = 1; off < 16; off <<= 1) s += __shfl_xor(s, off);
+      for (int c = 0; c < KC; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s = fmaf(qv[c][i], qv[c][i], s);
+      s += __shfl_xor(s, 16);
+      s += __shfl_xor(s, 32);
       qn2 = s + kL2Eps;
     }
     const float scale = g / sqrtf(ss * inv_norm + kRmsEps * qn2);
-    const int n = n0 + tok;
-    if (n < n_end) {
 #pragma unroll
-      for (int m = 0; m < VPT; ++m) {
-        const int c = part + 16 * m;
-        const size_t idx = ((size_t)fh * N + n) * DV + c;
-        if (c < dvo) obase[(size_t)n * ors + c] = TOKGATE ? o[m] * scale * gtok[idx] : o[m] * scale;
-      }
+    for (int mb = 0; mb < MB; ++mb) {
+      floatx4 y = acc[mb] * scale;
+      const uint32_t ch = mb * 16 + 4 * lg;
+      if constexpr (TOKGATE)
+        y *= __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                                             grsrc, (int)(((uint32_t)n * DV + ch) * 4u), 0, 0));
+      // Channels past dvo (zero padding of a narrow head) are not stored.
+      store_b128(orsrc, (int)ch < dvo ? ((uint32_t)n * ors + ch) * 4u : kOutOfRange,
+                 __builtin_bit_cast(u32x4, y));
     }
   }
 }
@@ -370,26 +436,53 @@ inline int readout_chunks(long long fh_count, int N) {
   return c < 1 ? 1 : (int)c;
 }
 
+// fp32 storage: workgroups per frame.  The kernel is bound by the matrix
+// rate, which the workgroups of a compute unit share, so what matters is an
+// even load over the compute units: a launch takes about as many 64-token
+// steps as the busiest one has, and something like one more per workgroup
+// for the state prologue.  The smallest count that minimises it is used (84
+// frames of 1560 tokens: 3 workgroups, 252 in all).
+inline int readout_f32_chunks(long long fh_count, int N) {
+  const long long cus = 256;
+  const int steps = (N + 63) / 64;
+  int best = 1;
+  long long best_cost = -1;
+  for (int c = 1; c <= steps && c <= 32; ++c) {
+    const long long cost = ((fh_count * c + cus - 1) / cus) * ((steps + c - 1) / c + 1);
+    if (best_cost < 0 || cost < best_cost) best = c, best_cost = cost;
+  }
+  return best;
+}
+
 template <int DK, int DV>
 hipError_t launch_readout_t(bool is_f32, const void* q, const float* S_fwd, const float* S_rev,
                             const float* gate, int F, int N, int H, int d_v_norm,
                             const GatherOptions& go, void* out, hipStream_t stream) {
   const long long fh_count = (long long)H * F;
+  const bool genout = go.out_heads > 1 || d_v_norm != DV || go.q_heads > 1 || go.q_l2;
+  const int ql2 = go.q_l2 ? 1 : 0;
+  if (is_f32) {
+    const int chunks = readout_f32_chunks(fh_count, N);
+    const dim3 grid((unsigned)(fh_count * chunks));
+#define VDA_READOUT_F32(TG)                                                                      \
+  hipLaunchKernelGGL((readout_f32_kernel<DK, DV, TG>), grid, dim3(kThreads), 0, stream,          \
+                     static_cast<const float*>(q), S_fwd, S_rev, gate, F, N, chunks, grid.x,     \
+                     d_v_norm, go.out_heads, go.q_heads, ql2, go.alpha, go.chunk, go.radius,     \
+                     go.offset, static_cast<const float*>(go.gate_tokens),                       \
+                     static_cast<float*>(out))
+    if (go.gate_tokens != nullptr)
+      VDA_READOUT_F32(true);
+    else
+      VDA_READOUT_F32(false);
+#undef VDA_READOUT_F32
+    return hipGetLastError();
+  }
   const int chunks = readout_chunks(fh_count, N);
   int tpc = (N + chunks - 1) / chunks;
   tpc = ((tpc + 63) / 64) * 64;
   const dim3 grid((unsigned)(fh_count * chunks));
-  const bool genout = go.out_heads > 1 || d_v_norm != DV || go.q_heads > 1 || go.q_l2;
-  const int ql2 = go.q_l2 ? 1 : 0;
 #define VDA_READOUT_LAUNCH(TG, GO)                                                                 \
-  if (is_f32)                                                                                      \
-    hipLaunchKernelGGL((readout_f32_kernel<DK, DV, TG>), grid, dim3(kThreads), 0, stream,          \
-                       static_cast<const float*>(q), S_fwd, S_rev, gate, F, N, chunks, tpc,       \
-                       d_v_norm, go.out_heads, go.q_heads, ql2, go.alpha, go.chunk, go.radius,     \
-                       go.offset,                                                                  \
-                       static_cast<const float*>(go.gate_tokens), static_cast<float*>(out));      \
-  else                                                                                             \
-    hipLaunchKernelGGL((readout_bf16_kernel<DK, DV, TG, GO>), grid, dim3(kThreads), 0, stream,     \
+  hipLaunchKernelGGL((readout_bf16_kernel<DK, DV, TG, GO>), grid, dim3(kThreads), 0, stream,       \
                        static_cast<const uint16_t*>(q), S_fwd, S_rev, gate, F, N, chunks, tpc,    \
                        (unsigned)(fh_count * chunks), d_v_norm, go.out_heads, go.q_heads, ql2,     \
                        go.alpha, go.chunk,                                                         \
