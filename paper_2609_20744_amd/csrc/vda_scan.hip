@@ -49,7 +49,9 @@ void scan_f32_kernel(const float* __restrict__ Mat, const float* __restrict__ Bm
   constexpr int XLD = DK + 4;        // LDS row stride (floats)
   constexpr int NB = DK / 16;        // 16-column output slices
   constexpr int NBW = (NB + 3) / 4;  // slices per wave
-  constexpr int KL = DK / 4;         // k values per lane and slice (k = lg * KL + s)
+  // k values per lane and slice: value s is k = 16 (s / 4) + 4 lg + s % 4, so
+  // the four lane groups of a row read one 64-byte run of it per load.
+  constexpr int KL = DK / 4;
   constexpr int E = DK / 16;         // state elements per thread in the row-wise phase
   static_assert(E % 2 == 0, "float2 granularity");
   // Row-wise accesses in 16-byte pieces where the row slice allows: fewer
@@ -102,28 +104,27 @@ void scan_f32_kernel(const float* __restrict__ Mat, const float* __restrict__ Bm
   float ops[kPrefetch][NBW][KL];
   float bs[kPrefetch][E];
   u32x4 al[kPrefetch];  // alpha, columns 4 tid .. 4 tid + 3 (threads tid < DK / 4)
-  auto load_ops = [&](int step, float (&op)[NBW][KL], float (&bb)[E], u32x4& av) {
-    const int frame = frame_of(step);
-    const int bframe = FROZEN ? frame_of(step - 1) : frame;
-    const bool bin = (unsigned)bframe < (unsigned)F;
-    const size_t fh = (size_t)hb * F + frame;
-    const float* mat = Mat + fh * (DK * DK);
+  // Values 4 c .. 4 c + 3 of every slice's operand of step `step`.
+  auto load_mat = [&](int step, int c, float (&op)[NBW][KL]) {
+    const float* mat = Mat + ((size_t)hb * F + frame_of(step)) * (DK * DK);
 #pragma unroll
     for (int m = 0; m < NBW; ++m) {
       const int nb = wave + 4 * m;
       if (NB >= 4 || nb < NB) {  // compile-time true unless d_k = 32
         // Mat[k][nb*16 + li] == Mat[nb*16 + li][k] (symmetric)
-        const float* row = mat + (size_t)(nb * 16 + li) * DK;
-#pragma unroll
-        for (int s = 0; s < KL; s += 4) {
-          const float4 v = *reinterpret_cast<const float4*>(row + lg * KL + s);
-          op[m][s] = v.x;
-          op[m][s + 1] = v.y;
-          op[m][s + 2] = v.z;
-          op[m][s + 3] = v.w;
-        }
+        const float4 v = *reinterpret_cast<const float4*>(mat + (size_t)(nb * 16 + li) * DK +
+                                                          16 * c + 4 * lg);
+        op[m][4 * c] = v.x;
+        op[m][4 * c + 1] = v.y;
+        op[m][4 * c + 2] = v.z;
+        op[m][4 * c + 3] = v.w;
       }
     }
+  };
+  auto load_add = [&](int step, float (&bb)[E], u32x4& av) {
+    const int frame = frame_of(step);
+    const int bframe = FROZEN ? frame_of(step - 1) : frame;
+    const bool bin = (unsigned)bframe < (unsigned)F;
 #pragma unroll
     for (int e = 0; e < E; e += VW) {
       const uint32_t off =
@@ -148,7 +149,9 @@ void scan_f32_kernel(const float* __restrict__ Mat, const float* __restrict__ Bm
 
 #pragma unroll
   for (int d = 0; d < kPrefetch; ++d) {
-    load_ops(min(d, F - 1), ops[d], bs[d], al[d]);
+    load_add(min(d, F - 1), bs[d], al[d]);
+#pragma unroll
+    for (int c = 0; c < KL / 4; ++c) load_mat(min(d, F - 1), c, ops[d]);
     __builtin_amdgcn_sched_barrier(0);
   }
   if constexpr (DECAY) {
@@ -193,38 +196,50 @@ void scan_f32_kernel(const float* __restrict__ Mat, const float* __restrict__ Bm
       if constexpr (DECAY) {  // alpha of the next step (this step's reads are done)
         if (tid < DK / 4) reinterpret_cast<u32x4*>(alds)[tid] = al[(d + 1) % kPrefetch];
       }
+      // Always refill (past the end: a clamped, unused frame) so no branch
+      // hides the loads from the wait-count bookkeeping.
+      const int refill = min(step + kPrefetch, F - 1);
+      load_add(refill, bs[d], al[d]);
       if (NB >= 4 || wave < NB) {
-        // A-operand: row li of the block at k = lg * KL + s.
+        // A-operand: row li of the block at the same k.
         float a[KL];
-        const float* xr = &xs[cur][li * XLD + lg * KL];
+        const float* xr = &xs[cur][li * XLD + 4 * lg];
 #pragma unroll
         for (int s = 0; s < KL; s += 4) {
-          const float4 v = *reinterpret_cast<const float4*>(xr + s);
+          const float4 v = *reinterpret_cast<const float4*>(xr + 4 * s);
           a[s] = v.x;
           a[s + 1] = v.y;
           a[s + 2] = v.z;
           a[s + 3] = v.w;
         }
+        // The slices advance together, even and odd k in separate
+        // accumulators (four independent chains at d_k = 128); each chunk's
+        // operand registers are refilled as soon as its products are issued.
+        // (Slice by slice on one chain, refilled after the last product, with
+        // 16-byte reads 128 bytes apart: 2.9 us a step at d_k = d_v = 128;
+        // 2.4 now, of which the products' issue is 0.9.)
+        floatx4 acc[NBW][2];
 #pragma unroll
-        for (int m = 0; m < NBW; ++m) {
-          const int nb = wave + 4 * m;
-          if (NB >= 4 || nb < NB) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < NBW; ++m) acc[m][0] = acc[m][1] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < KL; ++s) {
+        for (int c = 0; c < KL / 4; ++c) {
+#pragma unroll
+          for (int s = 4 * c; s < 4 * c + 4; ++s)
+#pragma unroll
+            for (int m = 0; m < NBW; ++m) {
               float b = ops[d][m][s];
               if constexpr (FROZEN)  // I - A / U
-                b = (lg * KL + s == nb * 16 + li ? 1.0f : 0.0f) - b * inv_u;
-              acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b, acc, 0, 0, 0);
+                b = (16 * c + 4 * lg + s % 4 == (wave + 4 * m) * 16 + li ? 1.0f : 0.0f) - b * inv_u;
+              acc[m][s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b, acc[m][s & 1], 0, 0, 0);
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) xs[cur ^ 1][(lg * 4 + i) * XLD + nb * 16 + li] = acc[i];
-          }
+          load_mat(refill, c, ops[d]);
         }
+#pragma unroll
+        for (int m = 0; m < NBW; ++m)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            xs[cur ^ 1][(lg * 4 + i) * XLD + (wave + 4 * m) * 16 + li] = acc[m][0][i] + acc[m][1][i];
       }
-      // Always refill (past the end: a clamped, unused frame) so no branch
-      // hides the loads from the wait-count bookkeeping.
-      load_ops(min(step + kPrefetch, F - 1), ops[d], bs[d], al[d]);
       cur ^= 1;
     }
   }
