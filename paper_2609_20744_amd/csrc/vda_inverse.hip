@@ -10,19 +10,17 @@
 namespace vda {
 namespace {
 
-// Three workgroups per SIMD (the registers of the tiled store would
-// otherwise push it to two), so one matrix's serial pivot work hides behind
-// the others' products.
+// Three waves per SIMD, so that three matrices of d_k = 128 share a compute
+// unit (576 frames are one round of 256 compute units; at two, 186 registers,
+// they took 53 us instead of 36).
 template <int DK, bool TILED>
-__global__ __launch_bounds__(64 * (DK / 16 < 4 ? DK / 16 : 4))
-__attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(inv::inverse_threads(DK)) __attribute__((amdgpu_waves_per_eu(3)))
 void inverse_kernel(const float* A_part, unsigned first_split, int plan_splits, unsigned extra,
                     size_t part_stride,
                     float* Inv,  // may alias A_part (in place)
                     float* B_part, size_t b_mat, size_t b_stride) {
-  constexpr int NB = DK / 16;
-  constexpr int W = NB < 4 ? NB : 4;
-  __shared__ __align__(16) float piv[3][NB][64 * 4];  // [buffer][block j][lane][4]
+  constexpr int kT = inv::inverse_threads(DK);
+  __shared__ __align__(16) float lds[inv::inverse_lds_floats(DK)];
 
   const int tid = threadIdx.x;
   if (blockIdx.x >= gridDim.x - extra) {
@@ -34,13 +32,13 @@ void inverse_kernel(const float* A_part, unsigned first_split, int plan_splits, 
     const size_t f = first_split + e / 4;
     const size_t quarter = b_mat / 4;
     inv::fold_b_partials(B_part + f * b_mat, plan_splits, (e % 4) * quarter,
-                         (e % 4 + 1) * quarter, b_stride, tid, 64 * W);
+                         (e % 4 + 1) * quarter, b_stride, tid, kT);
     return;
   }
   const size_t base = (size_t)blockIdx.x * (DK * DK);
   // Frames from first_split on were split into plan_splits token ranges.
   const int splits = blockIdx.x >= first_split ? plan_splits : 1;
-  inv::invert_matrix<DK, TILED>(A_part, splits, part_stride, base, Inv, &piv[0][0][0], tid);
+  inv::invert_matrix<DK, TILED>(A_part, splits, part_stride, base, Inv, lds, tid);
 }
 
 }  // namespace
@@ -61,26 +59,26 @@ hipError_t launch_frame_inverse(const float* A_part, float* B_part, SplitPlan pl
   switch (d_k) {
     case 32:
       if (tiled)
-        hipLaunchKernelGGL((inverse_kernel<32, true>), grid, dim3(64 * 2), 0, stream, A_part,
+        hipLaunchKernelGGL((inverse_kernel<32, true>), grid, dim3(inv::inverse_threads(32)), 0, stream, A_part,
                            first_split, splits, extra, part_stride, Inv, B_part, b_mat, b_stride);
       else
-        hipLaunchKernelGGL((inverse_kernel<32, false>), grid, dim3(64 * 2), 0, stream, A_part,
+        hipLaunchKernelGGL((inverse_kernel<32, false>), grid, dim3(inv::inverse_threads(32)), 0, stream, A_part,
                            first_split, splits, extra, part_stride, Inv, B_part, b_mat, b_stride);
       break;
     case 64:
       if (tiled)
-        hipLaunchKernelGGL((inverse_kernel<64, true>), grid, dim3(64 * 4), 0, stream, A_part,
+        hipLaunchKernelGGL((inverse_kernel<64, true>), grid, dim3(inv::inverse_threads(64)), 0, stream, A_part,
                            first_split, splits, extra, part_stride, Inv, B_part, b_mat, b_stride);
       else
-        hipLaunchKernelGGL((inverse_kernel<64, false>), grid, dim3(64 * 4), 0, stream, A_part,
+        hipLaunchKernelGGL((inverse_kernel<64, false>), grid, dim3(inv::inverse_threads(64)), 0, stream, A_part,
                            first_split, splits, extra, part_stride, Inv, B_part, b_mat, b_stride);
       break;
     case 128:
       if (tiled)
-        hipLaunchKernelGGL((inverse_kernel<128, true>), grid, dim3(64 * 4), 0, stream, A_part,
+        hipLaunchKernelGGL((inverse_kernel<128, true>), grid, dim3(inv::inverse_threads(128)), 0, stream, A_part,
                            first_split, splits, extra, part_stride, Inv, B_part, b_mat, b_stride);
       else
-        hipLaunchKernelGGL((inverse_kernel<128, false>), grid, dim3(64 * 4), 0, stream, A_part,
+        hipLaunchKernelGGL((inverse_kernel<128, false>), grid, dim3(inv::inverse_threads(128)), 0, stream, A_part,
                            first_split, splits, extra, part_stride, Inv, B_part, b_mat, b_stride);
       break;
     default:

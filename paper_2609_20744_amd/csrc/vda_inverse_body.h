@@ -1,42 +1,55 @@
 // Device code of step a2, Inv_t = (I + A_t)^{-1} (Eq. 5).
 //
 // I + A_t is symmetric positive definite with every eigenvalue >= 1 (A_t is
-// a Gram matrix weighted by beta >= 0; Appendix A.1), so Gauss-Jordan
-// elimination needs no pivoting and every leading block is invertible.
+// a Gram matrix weighted by beta >= 0; Appendix A.1), so elimination needs
+// no pivoting and every leading block is invertible.
 //
-// One workgroup inverts one d_k x d_k matrix in fp32 by blocked Gauss-Jordan
-// with 16 x 16 blocks on v_mfma_f32_16x16x4_f32.  Block rows are dealt out
-// to the waves (wave w owns rows w, w + W, ...), each held in MFMA
-// accumulator layout (block (i, j): lane (c, g) holds rows 4g..4g+3, column
-// c).  Block step kb:
-//   1. the owner of row kb inverts the pivot block D = M[kb][kb] by scalar
-//      Gauss-Jordan and publishes D^{-1} and the pivot row P_j = M[kb][j]
-//      in LDS;
-//   2. for its rows i != kb every wave applies
-//        M[i][j] -= M[i][kb] D^{-1} P_j,   M[i][kb] = -M[i][kb] D^{-1},
-//      and the owner of row kb sets M[kb][j] = D^{-1} P_j, M[kb][kb] = D^{-1}.
-// After eliminating block columns 0..kb-1 the matrix is [[X, Y], [Z, S]]
-// with X and S symmetric and Z = -Y^T, so M[i][kb] is the transpose of the
-// published P_i, negated when i < kb, and M[i][kb] D^{-1} is (up to that
-// sign) the transpose of R_i = D^{-1} P_i.  The A-operands a lane supplies
-// at k = 4g + s are therefore element s of its own slot of P_i or R_i, and
-// each wave forms R_i only for its own rows.  A block (i, j) with
-// j > kb that step j will overwrite (i < kb, or i > j) is not updated:
-// about a third of the products are skipped.  The owner of row kb + 1
-// publishes step kb + 1's pivot during step kb (it updates that row first,
-// then inverts the pivot block while the other waves do their products) and
-// applies step kb to its other rows at the start of step kb + 1; the LDS
-// pivot rows are triple buffered, so each block step needs one barrier.
-// With several matrices' workgroups per SIMD, one wave's serial pivot work
-// also hides behind another matrix's products.
-// Both A_t and its inverse are symmetric, so the column segments of the
-// accumulator layout are loaded (for the blocks on and below the diagonal,
-// the only ones read) and stored as contiguous row segments of the
-// transposed block (the result is the transpose of the computed inverse,
-// which equals it up to rounding).
+// One workgroup inverts one d_k x d_k matrix in fp32 by block sweeps with
+// 16 x 16 blocks on v_mfma_f32_16x16x4_f32.  Sweeping block kb, with
+// D = M[kb][kb] and the pivot row P_j = M[kb][j], sets
+//     M[i][j] -= P_i^T D^{-1} P_j   (i, j != kb),
+//     M[kb][j] = D^{-1} P_j,   M[kb][kb] = -D^{-1},
+// keeps the matrix symmetric at every step, and leaves -M^{-1} after all of
+// them.  So only one block of each symmetric pair is kept: half the
+// products, registers and loads of an unsymmetric elimination.  Block {i, j},
+// i > j, is held as M[j][i] until block j is swept, which is where it is
+// P_i of step j, and as M[i][j] from then on, where it is P_j of step i;
+// step j writes the new value P_i^T D^{-1} in that orientation directly.  A
+// block's accumulator layout (lane (c, g) holds rows 4g .. 4g+3, column c)
+// serves as the B-operand of the block and as the A-operand of its
+// transpose, so with R_j = D^{-1} P_j every update takes its operands as they
+// lie: M[j][i] -= R_j^T P_i before block j is swept, M[i][j] -= P_i^T R_j
+// after, with R_j for the wave's own columns only.
+//
+// Column j's blocks i = j .. NB-1 belong to one update wave, of which there
+// are three (one for d_k <= 64, whose products take less than a pivot
+// block).  One more wave, with a SIMD to itself when the compute unit has one
+// matrix, inverts the pivot blocks: during step kb, while the update waves
+// apply D^{-1} of block kb, it brings diagonal block kb + 1 up
+// to date from the published rows and inverts it by scalar Gauss-Jordan, so
+// that the chain of 16 pivots per block is all that is serial.  Each step
+// ends in one barrier, after which everything the next step reads is
+// published in LDS (double buffered): P_j and D^{-1} of that step, and the
+// diagonal block after it.
+//
 // The token-split partials of A_t are summed in split order while loading
 // (fold_b_partials does the same for B_t).  All products and sums are fp32.
+// Only A_t's blocks on and below the diagonal are read, as contiguous row
+// segments.  The result is exactly symmetric off the diagonal blocks.
+//
+// What bounds it (d_k = 128, shader-clock stamps, one matrix): the pivot
+// wave's chain, 8 x (1880 cycles of pivots, 117 each, + 700 for the next
+// block's operands and update), under which the update waves' ~60 products
+// of 32 cycles a step lie; then 3000 cycles each for loads and stores.  16
+// matrices of two partials 20.4 -> 13.8 us, 504 matrices 37.9 -> 27.4, 700
+// (100 frames x 7 heads) 46 -> 34, 1536 of d_k = 64 25.6 -> 21.8 (before: an
+// unsymmetric elimination of all 64 blocks in four waves, one of which
+// inverted the pivot block beside its own products).  With four update
+// waves and the pivot wave beside one of them on a SIMD, a pivot block took
+// 2900 cycles instead of 1880.
 #pragma once
+
+#include <type_traits>
 
 #include "vda_common.h"
 
@@ -45,17 +58,16 @@ namespace inv {
 
 // Pivot block inverse by scalar Gauss-Jordan: lane (li, lg) holds
 // D[4lg + r][li] in d[r] on entry and D^{-1} in the same layout on exit.
-// Every cross-lane move is a VALU operation, so a pivot costs no LDS round
-// trip: the pivot element comes from one lane (v_readlane), pivot row p
-// (held by lane group p/4) is copied to all four lane groups by a 16-lane
-// and a 32-lane row swap (v_permlane16_swap, v_permlane32_swap), and pivot
-// column p (held by lane p of every group) by a row broadcast (DPP
-// row_newbcast).  The reciprocal is the hardware estimate refined by one
-// Newton step (error <= 1 ulp); the IEEE division sequence would sit on the
-// serial path once per pivot.
-template <int P>
+// Every cross-lane move is a VALU operation.  The four rows of a lane group
+// are pivots in turn; copies of them, kept up to date in all four groups, are
+// made once per four pivots by a 16-lane and a 32-lane row swap
+// (v_permlane16_swap, v_permlane32_swap), so a pivot step reads its row and
+// its pivot (DPP row_newbcast, as are the columns, folded into the
+// multiply-adds) from its own lanes.  The reciprocal is the hardware
+// estimate refined by one Newton step (error <= 1 ulp); the IEEE division
+// sequence would sit on the serial path once per pivot.
+template <int G>
 __device__ __forceinline__ float row_of_group(float x) {
-  constexpr int G = P >> 2;
   const uint32_t u = __float_as_uint(x);
   const auto t = __builtin_amdgcn_permlane16_swap(u, u, false, false);  // [r0 r0 r2 r2], [r1 r1 r3 r3]
   const uint32_t y = (G & 1) ? t[1] : t[0];
@@ -64,233 +76,321 @@ __device__ __forceinline__ float row_of_group(float x) {
 }
 
 template <int P>
-__device__ __forceinline__ void pivot_step(float (&d)[4], int li, int lg) {
+__device__ __forceinline__ float lane_of_row(float x) {  // lane P of each row of 16, in all of them
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + P, 0xf, 0xf, false));
+}
+
+// Pivot P = 4 G + E; row[f], f >= E: row 4 G + f in every lane group.
+template <int P>
+__device__ __forceinline__ void pivot_step(float (&d)[4], float (&row)[4], int li, int lg) {
   constexpr int G = P >> 2, E = P & 3;
-  const float rowv = row_of_group<P>(d[E]);                                // D[P][li]
-  float colv[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r)                                              // D[4lg+r][P]
-    colv[r] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(d[r]), 0x150 + P, 0xf, 0xf,
-                                                      false));
-  const float piv = __int_as_float(
-      __builtin_amdgcn_readlane(__float_as_int(d[E]), P + 16 * G));        // D[P][P]
-  float inv = __builtin_amdgcn_rcpf(piv);
-  inv = inv * fmaf(-piv, inv, 2.0f);
+  float inv = __builtin_amdgcn_rcpf(lane_of_row<P>(row[E]));
+  inv = inv * fmaf(lane_of_row<P>(row[E]), -inv, 2.0f);
   const bool on_col = li == P;
-  const float rs = rowv * inv;                                             // new pivot row
-  // One fused update for every element off the pivot row: d - colv * s with
-  // s = rs, and in the pivot column (where colv = d) s = 1 + inv, which
-  // gives -d * inv, the eliminated column.
-  const float s = on_col ? 1.0f + inv : rs;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) d[r] = fmaf(-colv[r], s, d[r]);
-  if (lg == G) d[E] = on_col ? inv : rs;                                   // pivot row
+  const float x = on_col ? 1.0f : row[E];
+  const float m = on_col ? -1.0f : 0.0f;
+  // One fused update for every element off the pivot row, d + column * ns,
+  // with ns = -(new pivot row), and in the pivot column (where the column is
+  // d) ns = -(1 + inv), which gives -d * inv, the eliminated column.
+  const float ns = fmaf(x, -inv, m);
+  // x += (lane P of x's row) * ns, one instruction each.  The wait states are
+  // those a DPP read needs after a VALU write of its register, whoever wrote
+  // it; the rows come first, so that the ones read next are old enough
+  // when the block ends.
+#define VDA_COL(x) "v_fmac_f32_dpp " x ", " x ", %[ns] row_newbcast:%[p] row_mask:0xf bank_mask:0xf\n\t"
+#define VDA_COLS VDA_COL("%[d0]") VDA_COL("%[d1]") VDA_COL("%[d2]") VDA_COL("%[d3]")
+#define VDA_D [d0] "+v"(d[0]), [d1] "+v"(d[1]), [d2] "+v"(d[2]), [d3] "+v"(d[3])
+  if constexpr (E == 0)
+    asm("s_nop 1\n\t" VDA_COL("%[r1]") VDA_COL("%[r2]") VDA_COL("%[r3]") VDA_COLS
+        : VDA_D, [r1] "+v"(row[1]), [r2] "+v"(row[2]), [r3] "+v"(row[3]) : [ns] "v"(ns), [p] "n"(P));
+  else if constexpr (E == 1)
+    asm("s_nop 1\n\t" VDA_COL("%[r2]") VDA_COL("%[r3]") VDA_COLS
+        : VDA_D, [r2] "+v"(row[2]), [r3] "+v"(row[3]) : [ns] "v"(ns), [p] "n"(P));
+  else if constexpr (E == 2)
+    asm("s_nop 1\n\t" VDA_COL("%[r3]") VDA_COLS
+        : VDA_D, [r3] "+v"(row[3]) : [ns] "v"(ns), [p] "n"(P));
+  else
+    asm("s_nop 1\n\t" VDA_COLS : VDA_D : [ns] "v"(ns), [p] "n"(P));
+#undef VDA_COL
+#undef VDA_COLS
+#undef VDA_D
+  if (lg == G) d[E] = x * inv;  // the new pivot row
 }
 
-template <int P = 0>
+template <int G = 0>
 __device__ __forceinline__ void invert_pivot_block(float (&d)[4], int li, int lg) {
-  pivot_step<P>(d, li, lg);
-  if constexpr (P + 1 < 16) invert_pivot_block<P + 1>(d, li, lg);
+  float row[4];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) row[f] = row_of_group<G>(d[f]);
+  pivot_step<4 * G>(d, row, li, lg);
+  pivot_step<4 * G + 1>(d, row, li, lg);
+  pivot_step<4 * G + 2>(d, row, li, lg);
+  pivot_step<4 * G + 3>(d, row, li, lg);
+  if constexpr (G + 1 < 4) invert_pivot_block<G + 1>(d, li, lg);
 }
 
-// D^{-1} of step kb from the pivot buffer pb: accumulator layout, and (being
-// symmetric) its own A-operand D^{-1}[li][4lg+s] = d[s].
-__device__ __forceinline__ void read_pivot_inverse(const float* pb, int kb, int lane, float (&d)[4]) {
-  const float4 v = *reinterpret_cast<const float4*>(pb + (kb * 64 + lane) * 4);
-  d[0] = v.x;
-  d[1] = v.y;
-  d[2] = v.z;
-  d[3] = v.w;
+// Floats of LDS that inverting one matrix takes: two sets of NB published
+// blocks, two diagonal blocks, and two 16 x 16 blocks (row stride 20) per
+// update wave for the transposes of the output.
+__host__ __device__ constexpr int inverse_update_waves(int dk) { return dk == 128 ? 3 : 1; }
+__host__ __device__ constexpr int inverse_threads(int dk) { return 64 * (inverse_update_waves(dk) + 1); }
+__host__ __device__ constexpr int inverse_lds_floats(int dk) {
+  return 2 * (dk / 16) * 256 + 2 * 256 + inverse_update_waves(dk) * 2 * 320;
 }
 
-// The owner of pivot row kb inverts its pivot block D = row[kb] and
-// publishes D^{-1} (in slot kb) and P_j = row[j] (j != kb) in pb.
-template <int NB>
-__device__ __forceinline__ void publish_pivot(const floatx4 (&row)[NB], int kb, float* pb, int li,
-                                              int lg, int lane) {
-  const floatx4 dd = row[kb];
-  float d[4] = {dd[0], dd[1], dd[2], dd[3]};
-  // The pivot block is this matrix's critical path: while it runs, the
-  // SIMD's arbiter prefers this wave over the other matrices' waves.
-  __builtin_amdgcn_s_setprio(2);
-  invert_pivot_block(d, li, lg);
-  __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const floatx4 v = j == kb ? floatx4{d[0], d[1], d[2], d[3]} : row[j];
-    *reinterpret_cast<float4*>(pb + (j * 64 + lane) * 4) = make_float4(v[0], v[1], v[2], v[3]);
-  }
+__device__ __forceinline__ floatx4 read_block(const float* b, int lane) {
+  return reinterpret_cast<const floatx4*>(b)[lane];
 }
 
-// Block step kb for block row i (held in row[]), from step kb's published
-// D^{-1} (d) and pivot row P_j (pb).
-template <int NB>
-__device__ __forceinline__ void update_row(floatx4 (&row)[NB], int i, int kb, const float* pb,
-                                           const float (&d)[4], int lane) {
-  if (i == kb) {
-    // The pivot row: M[kb][j] = D^{-1} P_j from this wave's own P_j.
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (j == kb) continue;
-      const floatx4 pj = row[j];
-      floatx4 r = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 4; ++s) r = __builtin_amdgcn_mfma_f32_16x16x4f32(d[s], pj[s], r, 0, 0, 0);
-      row[j] = r;
-    }
-    row[kb] = floatx4{d[0], d[1], d[2], d[3]};
-    return;
-  }
-  // Row i != kb.  With sigma = +1 for i > kb and -1 for i < kb,
-  // M[i][kb] = sigma P_i^T, so C_i = M[i][kb] D^{-1} = sigma R_i^T with
-  // R_i = D^{-1} P_i, and
-  //   M[i][j] -= C_i P_j  (j != kb),   M[i][kb] = -C_i.
-  // A-operands at k = 4lg + s: -M[i][kb] -> -sigma P_i[s] and
-  // -C_i -> -sigma R_i[s]; B-operands P_j[s] and D^{-1}: d[s].
-  const float4 p4 = *reinterpret_cast<const float4*>(pb + (i * 64 + lane) * 4);
-  const float pi[4] = {p4.x, p4.y, p4.z, p4.w};
-  const float ms = i > kb ? -1.0f : 1.0f;  // -sigma
-  floatx4 o = {0.f, 0.f, 0.f, 0.f};
-  floatx4 ri = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    o = __builtin_amdgcn_mfma_f32_16x16x4f32(ms * pi[s], d[s], o, 0, 0, 0);
-    ri = __builtin_amdgcn_mfma_f32_16x16x4f32(d[s], pi[s], ri, 0, 0, 0);
-  }
-  float c[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) c[s] = ms * ri[s];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    // Block (i, j), j > kb, is overwritten at step j (from the pivot row's
-    // transpose) unless kb < i <= j: skip those dead updates.
-    if (j == kb || (j > kb && (i > j || i < kb))) continue;
-    const float4 pj = *reinterpret_cast<const float4*>(pb + (j * 64 + lane) * 4);
-    row[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[0], pj.x, row[j], 0, 0, 0);
-    row[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[1], pj.y, row[j], 0, 0, 0);
-    row[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[2], pj.z, row[j], 0, 0, 0);
-    row[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(c[3], pj.w, row[j], 0, 0, 0);
-  }
-  row[kb] = o;
+__device__ __forceinline__ void write_block(float* b, int lane, floatx4 v) {
+  reinterpret_cast<floatx4*>(b)[lane] = v;
 }
 
-// The elimination for the block rows of wave WV (rows WV, WV + W, ...); a
-// template on the wave so that every row-dependent condition is resolved at
-// compile time.  All W waves of the workgroup take the same NB barriers.
+// Block (i, j), i >= j, of I + A_t, held as M[j][i]: lane (li, lg) holds
+// M[16j + 4lg + s][16i + li], which by symmetry is a 16-byte piece of row
+// 16i + li.
+template <int DK>
+__device__ __forceinline__ floatx4 load_block(const float* m, int i, int j, int li, int lg) {
+  return *reinterpret_cast<const floatx4*>(m + (size_t)(16 * i + li) * DK + 16 * j + 4 * lg);
+}
+
+__device__ __forceinline__ void add_identity(floatx4& b, int li, int lg) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+    if (4 * lg + s == li) b[s] += 1.0f;
+}
+
+// Columns of update wave WV.  With NB = 8 three waves share the 36 blocks in
+// whole columns (column j has NB - j), 12 each; with fewer blocks one wave
+// has them all.
+template <int NB, int WV>
+struct WaveColumns {
+  static constexpr int count = NB == 8 ? (WV == 2 ? 4 : 2) : NB;
+  static constexpr int col(int c) {
+    if (NB == 8) return WV == 0 ? (c == 0 ? 0 : 4) : WV == 1 ? (c == 0 ? 1 : 3) : (c == 0 ? 2 : 4 + c);
+    return c;
+  }
+};
+
+// One update wave.
 template <int DK, int WV, bool TILED>
-__device__ __forceinline__ void invert_rows(const float* A_part, int splits, size_t part_stride,
-                                            size_t base, float* Inv, float (*piv)[DK / 16][64 * 4],
-                                            int lane) {
-  constexpr int NB = DK / 16;          // 16-wide blocks per side
-  constexpr int W = NB < 4 ? NB : 4;   // waves
-  constexpr int RPW = NB / W;          // block rows per wave
-  const int li = lane & 15;
-  const int lg = lane >> 4;
+struct UpdateWave {
+  static constexpr int NB = DK / 16;
+  using Cols = WaveColumns<NB, WV>;
+  static constexpr int NC = Cols::count;
+  static constexpr int CMIN = Cols::col(0);
 
-  // acc[q][j]: block (i, j) with i = WV + W q.  Its accumulator holds the
-  // column segment M[16i + 4lg .. +3][16j + li].  Only the blocks of A_t on
-  // and below the diagonal are read (the statistics may leave the others
-  // unwritten): for j >= i, A_t is symmetric, so the segment is read as the
-  // contiguous row segment M[16j + li][16i + 4lg .. +3] of block (j, i) with
-  // one 16-byte load (and the result is written back the same way); for
-  // j < i, straight from block (i, j) as four scalars.
-  // All blocks of this wave's rows of one partial are loaded in one memory
-  // round trip: the first partial straight into the accumulators, each
-  // further token range of a split frame into a staging set that is then
-  // added in range order (one round trip per partial).
-  auto load_block = [&](const float* m, int i, int j) -> floatx4 {
-    if (j >= i)
-      return *reinterpret_cast<const floatx4*>(m + (size_t)(16 * j + li) * DK + 16 * i + 4 * lg);
-    const float* p = m + (size_t)(16 * i + 4 * lg) * DK + 16 * j + li;
-    return floatx4{p[0], p[DK], p[2 * DK], p[3 * DK]};
-  };
-  floatx4 acc[RPW][NB];
-  const float* a0 = A_part + base;
-#pragma unroll
-  for (int q = 0; q < RPW; ++q)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) acc[q][j] = load_block(a0, WV + W * q, j);
-  for (int s = 1; s < splits; ++s) {
-    floatx4 x[RPW][NB];
-#pragma unroll
-    for (int q = 0; q < RPW; ++q)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) x[q][j] = load_block(a0 + s * part_stride, WV + W * q, j);
-#pragma unroll
-    for (int q = 0; q < RPW; ++q)
-#pragma unroll
-      for (int j = 0; j < NB; ++j) acc[q][j] += x[q][j];
-  }
-#pragma unroll
-  for (int q = 0; q < RPW; ++q) {
-    const int i = WV + W * q;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (4 * lg + r == li) acc[q][i][r] += 1.0f;
-  }
+  floatx4 a[NC][NB];  // blocks {i, col(c)}, i >= col(c)
+  float* pub;         // [2][NB][256] published blocks
+  float* diag;        // [2][256] the next diagonal block
+  int lane, li, lg;
 
-  // Step kb's pivot is published by the owner of row kb during step kb - 1
-  // (step 0's before the loop): it applies step kb - 1 to row kb first,
-  // inverts the new pivot block and publishes it, and defers step kb - 1 for
-  // its other rows to the start of step kb.  So the serial pivot chain runs
-  // while the other waves do their products, and the pivot buffers are
-  // triple buffered (a deferred update still reads step kb - 1's).
-  if (WV == 0) publish_pivot<NB>(acc[0], 0, &piv[0][0][0], li, lg, lane);
+  __device__ __forceinline__ void load(const float* A_part, int splits, size_t part_stride) {
 #pragma unroll
-  for (int kb = 0; kb < NB; ++kb) {
-    lds_barrier();
-    if (kb >= 1 && kb % W == WV) {  // deferred: step kb - 1 for this wave's other rows
-      const float* pp = &piv[(kb - 1) % 3][0][0];
-      float dp[4];
-      read_pivot_inverse(pp, kb - 1, lane, dp);
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int q = 0; q < RPW; ++q)
-        if (WV + W * q != kb) update_row<NB>(acc[q], WV + W * q, kb - 1, pp, dp, lane);
+      for (int i = Cols::col(c); i < NB; ++i) a[c][i] = load_block<DK>(A_part, i, Cols::col(c), li, lg);
+    // Further token ranges of a split frame, two per memory round trip.
+    for (int s = 1; s < splits; s += 2) {
+      const float* m0 = A_part + s * part_stride;
+      const bool two = s + 1 < splits;
+      const float* m1 = two ? m0 + part_stride : m0;
+      floatx4 x[NC][NB], y[NC][NB];
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = Cols::col(c); i < NB; ++i) {
+          x[c][i] = load_block<DK>(m0, i, Cols::col(c), li, lg);
+          y[c][i] = load_block<DK>(m1, i, Cols::col(c), li, lg);
+        }
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = Cols::col(c); i < NB; ++i) {
+          a[c][i] += x[c][i];
+          if (two) a[c][i] += y[c][i];
+        }
     }
-    const float* pb = &piv[kb % 3][0][0];
-    float d[4];
-    read_pivot_inverse(pb, kb, lane, d);
-    if (kb + 1 < NB && (kb + 1) % W == WV) {
-      const int qa = (kb + 1) / W;
-      update_row<NB>(acc[qa], kb + 1, kb, pb, d, lane);
-      publish_pivot<NB>(acc[qa], kb + 1, &piv[(kb + 1) % 3][0][0], li, lg, lane);
-    } else {
 #pragma unroll
-      for (int q = 0; q < RPW; ++q) update_row<NB>(acc[q], WV + W * q, kb, pb, d, lane);
-    }
+    for (int c = 0; c < NC; ++c) add_identity(a[c][Cols::col(c)], li, lg);
   }
 
-  if constexpr (TILED) {
-    // Split-bf16 operand tiles (operand_tile_offset): block (i, j) at lane
-    // (li, lg) holds X[16i + 4lg + r][16j + li], which is half i % 2 of that
-    // lane's B-operand of tile (nb = j, ks = i / 2), so every lane writes
-    // its own 8-byte halves with no exchange.
-    char* t0 = reinterpret_cast<char*>(Inv + base);
+  // Publishes what step KB reads of this wave's columns: P_j of that step and
+  // the diagonal block after its pivot.
+  template <int KB>
+  __device__ __forceinline__ void publish() const {
+    if constexpr (KB < NB) {
+      float* pb = pub + (KB & 1) * (NB * 256);
 #pragma unroll
-    for (int q = 0; q < RPW; ++q) {
-      const int i = WV + W * q;
+      for (int c = 0; c < NC; ++c) {
+        const int C = Cols::col(c);
+        if (C < KB) write_block(pb + C * 256, lane, a[c][KB]);
+        if (C == KB) {
 #pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const floatx4 a = acc[q][j];
-        const uint32_t h01 = pack_bf16x2(a[0], a[1]);
-        const uint32_t h23 = pack_bf16x2(a[2], a[3]);
-        const uint32_t l01 = pack_bf16x2(a[0] - bf16_lo(h01), a[1] - bf16_hi(h01));
-        const uint32_t l23 = pack_bf16x2(a[2] - bf16_lo(h23), a[3] - bf16_hi(h23));
-        char* t = t0 + operand_tile_offset(DK, 0, j, i / 2, lane) + (i & 1) * 8;
-        *reinterpret_cast<uint2*>(t) = make_uint2(h01, h23);
-        *reinterpret_cast<uint2*>(t + (size_t)DK * DK * 2) = make_uint2(l01, l23);
+          for (int i = KB + 1; i < NB; ++i) write_block(pb + i * 256, lane, a[c][i]);
+        }
+        if (C == KB + 1) write_block(diag + (KB & 1) * 256, lane, a[c][C]);
       }
     }
-  } else {
+  }
+
+  template <int KB>
+  __device__ __forceinline__ void step() {
+    const float* pb = pub + (KB & 1) * (NB * 256);
+    const floatx4 d = read_block(pb + KB * 256, lane);  // D^{-1}
+    floatx4 p[NB];
 #pragma unroll
-    for (int q = 0; q < RPW; ++q) {
-      const int i = WV + W * q;
+    for (int i = CMIN; i < NB; ++i)
+      if (i != KB) p[i] = read_block(pb + i * 256, lane);
+    const floatx4 z = {0.f, 0.f, 0.f, 0.f};
+    // -R_C of the wave's columns (D^{-1} is symmetric: d serves as its
+    // A-operand).
+    floatx4 r[NC];
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
-        *reinterpret_cast<float4*>(Inv + base + (size_t)(16 * j + li) * DK + 16 * i + 4 * lg) =
-            make_float4(acc[q][j][0], acc[q][j][1], acc[q][j][2], acc[q][j][3]);
+    for (int c = 0; c < NC; ++c) r[c] = z;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        if (Cols::col(c) != KB)
+          r[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(-d[s], p[Cols::col(c)][s], r[c], 0, 0, 0);
+    floatx4 t[NB];  // the new blocks of column KB, if it is one of the wave's
+#pragma unroll
+    for (int i = KB + 1; i < NB; ++i) t[i] = z;
+    // Products over the blocks in turn, so that the four of one block are
+    // far apart.  The diagonal block of the next pivot is left to the pivot
+    // wave.
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int C = Cols::col(c);
+#pragma unroll
+        for (int i = C; i < NB; ++i) {
+          if (i == KB || (i == C && C == KB + 1)) continue;
+          if (C == KB)
+            t[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][i][s], d[s], t[i], 0, 0, 0);
+          else if (C > KB)
+            a[c][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[c][s], p[i][s], a[c][i], 0, 0, 0);
+          else
+            a[c][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i][s], r[c][s], a[c][i], 0, 0, 0);
+        }
+      }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int C = Cols::col(c);
+      if (C == KB) {
+#pragma unroll
+        for (int i = KB + 1; i < NB; ++i) a[c][i] = t[i];
+        a[c][KB] = -d;
+      }
+      if (C < KB) a[c][KB] = -r[c];
+    }
+    publish<KB + 1>();
+    if constexpr (KB + 1 < NB) {
+      lds_barrier();
+      step<KB + 1>();
     }
   }
+
+  // Column C of the result X = -M to Inv: block {i, C} as it is held
+  // (M[i][C]) and, through this wave's LDS, transposed.
+  template <int C>
+  __device__ __forceinline__ void store_column(const floatx4 (&m)[NB], float* Inv, float* tp) const {
+    char* t0 = reinterpret_cast<char*>(Inv);
+    u32x2 hi[NB], lo[NB];
+#pragma unroll
+    for (int i = C; i < NB; ++i) {
+      const floatx4 x = -m[i];
+      floatx4 xt;  // X[16i + li][16C + 4lg + r]
+      if (i > C) {
+        float* b = tp + ((i - C) & 1) * 320;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) b[(4 * lg + s) * 20 + li] = x[s];
+        __builtin_amdgcn_wave_barrier();
+        xt = *reinterpret_cast<const floatx4*>(b + li * 20 + 4 * lg);
+        __builtin_amdgcn_wave_barrier();
+      }
+      if constexpr (TILED) {
+        // Split-bf16 operand tiles (operand_tile_offset): block (k, n) at lane
+        // (li, lg) holds X[16k + 4lg + r][16n + li], which is half k % 2 of
+        // that lane's 16 bytes of tile (nb = n, ks = k / 2).
+        split_block(x, hi[i], lo[i]);
+        if ((i & 1) == 1 && i > C) {
+          char* t = t0 + operand_tile_offset(DK, 0, C, i / 2, lane);
+          *reinterpret_cast<u32x4*>(t) = u32x4{hi[i - 1][0], hi[i - 1][1], hi[i][0], hi[i][1]};
+          *reinterpret_cast<u32x4*>(t + (size_t)DK * DK * 2) =
+              u32x4{lo[i - 1][0], lo[i - 1][1], lo[i][0], lo[i][1]};
+        } else if ((i & 1) == 1) {  // the diagonal block alone in its pair
+          char* t = t0 + operand_tile_offset(DK, 0, C, i / 2, lane) + 8;
+          *reinterpret_cast<u32x2*>(t) = hi[i];
+          *reinterpret_cast<u32x2*>(t + (size_t)DK * DK * 2) = lo[i];
+        }
+        if (i > C) {
+          u32x2 ht, lt;
+          split_block(xt, ht, lt);
+          char* t = t0 + operand_tile_offset(DK, 0, i, C / 2, lane) + (C & 1) * 8;
+          *reinterpret_cast<u32x2*>(t) = ht;
+          *reinterpret_cast<u32x2*>(t + (size_t)DK * DK * 2) = lt;
+        }
+      } else {
+        *reinterpret_cast<floatx4*>(Inv + (size_t)(16 * C + li) * DK + 16 * i + 4 * lg) = x;
+        if (i > C)
+          *reinterpret_cast<floatx4*>(Inv + (size_t)(16 * i + li) * DK + 16 * C + 4 * lg) = xt;
+      }
+    }
+  }
+
+  static __device__ __forceinline__ void split_block(floatx4 x, u32x2& hi, u32x2& lo) {
+    const uint32_t h01 = pack_bf16x2(x[0], x[1]), h23 = pack_bf16x2(x[2], x[3]);
+    hi = u32x2{h01, h23};
+    lo = u32x2{pack_bf16x2(x[0] - bf16_lo(h01), x[1] - bf16_hi(h01)),
+               pack_bf16x2(x[2] - bf16_lo(h23), x[3] - bf16_hi(h23))};
+  }
+
+  __device__ __forceinline__ void run(const float* A_part, int splits, size_t part_stride,
+                                      float* Inv, float* tp) {
+    load(A_part, splits, part_stride);
+    publish<0>();
+    lds_barrier();
+    step<0>();
+    store_column<Cols::col(0)>(a[0], Inv, tp);
+    if constexpr (NC > 1) store_column<Cols::col(1)>(a[1], Inv, tp);
+    if constexpr (NC > 2) store_column<Cols::col(2)>(a[2], Inv, tp);
+    if constexpr (NC > 3) store_column<Cols::col(3)>(a[3], Inv, tp);
+  }
+};
+
+// The pivot wave: D^{-1} of every block step, one step ahead of the update
+// waves.
+template <int DK>
+__device__ __forceinline__ void run_pivot_wave(const float* A_part, int splits, size_t part_stride,
+                                               float* pub, const float* diag, int lane) {
+  constexpr int NB = DK / 16;
+  const int li = lane & 15, lg = lane >> 4;
+  // The pivot blocks are this matrix's critical path: the SIMD's arbiter
+  // prefers this wave over the update waves it shares the SIMD with.
+  __builtin_amdgcn_s_setprio(2);
+  floatx4 d = load_block<DK>(A_part, 0, 0, li, lg);
+  for (int s = 1; s < splits; ++s) d += load_block<DK>(A_part + s * part_stride, 0, 0, li, lg);
+  add_identity(d, li, lg);
+  for (int kb = 0; kb < NB; ++kb) {
+    float e[4] = {d[0], d[1], d[2], d[3]};
+    invert_pivot_block(e, li, lg);
+    const floatx4 inv = {e[0], e[1], e[2], e[3]};
+    write_block(pub + ((kb & 1) * NB + kb) * 256, lane, inv);
+    lds_barrier();  // step kb is published
+    if (kb + 1 < NB) {
+      d = read_block(diag + (kb & 1) * 256, lane);
+      const floatx4 p = read_block(pub + ((kb & 1) * NB + kb + 1) * 256, lane);
+      floatx4 r = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) r = __builtin_amdgcn_mfma_f32_16x16x4f32(-inv[s], p[s], r, 0, 0, 0);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(r[s], p[s], d, 0, 0, 0);
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
 }
 
 // Sum the token-split partials of B_t into the first one (in place, in
@@ -329,30 +429,43 @@ __device__ __forceinline__ void fold_b_partials(float* b0, int splits, size_t lo
   }
 }
 
-// Invert one matrix with the first min(4, d_k/16) waves of the workgroup
-// (any further waves only take part in the barriers); `piv` is
-// 3 * (d_k/16) * 256 floats of LDS.  The matrix is the sum of `splits`
-// partials at A_part + s * part_stride + base; the result goes to Inv + base
-// (which may alias the first partial): an fp32 d_k x d_k matrix, or with
+// Inverts one matrix with the inverse_threads(DK) threads of the workgroup;
+// `lds` is inverse_lds_floats(DK) floats, 16-byte aligned.  The matrix is the
+// sum of `splits` partials at A_part + s * part_stride + base; the result
+// goes to Inv + base (which may alias the first partial: every wave has read
+// its blocks before the first barrier): an fp32 d_k x d_k matrix, or with
 // TILED the split-bf16 operand tiles of the same size in bytes.
 template <int DK, bool TILED>
 __device__ __forceinline__ void invert_matrix(const float* A_part, int splits, size_t part_stride,
-                                              size_t base, float* Inv, float* piv_lds, int tid) {
-  constexpr int NB = DK / 16;
-  constexpr int W = NB < 4 ? NB : 4;
-  auto piv = reinterpret_cast<float (*)[NB][64 * 4]>(piv_lds);
+                                              size_t base, float* Inv, float* lds, int tid) {
+  constexpr int NB = DK / 16, W = inverse_update_waves(DK);
+  float* pub = lds;
+  float* diag = pub + 2 * NB * 256;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (wave >= W) {  // a workgroup with more waves: the others only keep the barriers
-    for (int kb = 0; kb < NB; ++kb) lds_barrier();
-    return;
-  }
-  switch (wave) {
-    case 0: invert_rows<DK, 0, TILED>(A_part, splits, part_stride, base, Inv, piv, lane); break;
-    case 1: invert_rows<DK, 1 % W, TILED>(A_part, splits, part_stride, base, Inv, piv, lane); break;
-    case 2: invert_rows<DK, 2 % W, TILED>(A_part, splits, part_stride, base, Inv, piv, lane); break;
-    default: invert_rows<DK, 3 % W, TILED>(A_part, splits, part_stride, base, Inv, piv, lane); break;
-  }
+  // The wave's role; 256 workgroups apart, likely on the same compute unit,
+  // the roles lie on different SIMDs, so that pivot waves do not share one.
+  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) + (W == 3 ? blockIdx.x >> 8 : 0)) % (W + 1);
+  float* tp = diag + 2 * 256 + wave * 640;
+  const float* a = A_part + base;
+  float* out = Inv + base;
+  auto update = [&](auto wv) {
+    UpdateWave<DK, decltype(wv)::value, TILED> u;
+    u.pub = pub;
+    u.diag = diag;
+    u.lane = lane;
+    u.li = lane & 15;
+    u.lg = lane >> 4;
+    u.run(a, splits, part_stride, out, tp);
+  };
+  // Every branch takes the same NB barriers.
+  if (wave == W)
+    run_pivot_wave<DK>(a, splits, part_stride, pub, diag, lane);
+  else if (wave == 0)
+    update(std::integral_constant<int, 0>{});
+  else if (wave == 1)
+    update(std::integral_constant<int, 1 % W>{});
+  else
+    update(std::integral_constant<int, 2 % W>{});
 }
 
 }  // namespace inv
