@@ -7,18 +7,30 @@
 // stored for the readout.
 //
 // Work split as in the other scans: one workgroup per (head, direction,
-// 16-row block of the state); the rows of the state evolve independently,
-// and the block stays in LDS across all F frames.  The difference is how
-// Inv_t reaches the matrix cores: the inverse step wrote it as split-bf16
-// operand tiles (operand_tile_offset), in exactly the lane order of the
-// B-operands of v_mfma_f32_16x16x32_bf16.  Each wave loads the tiles of its
-// own 16-column output slices straight into registers, one contiguous 1 KB
-// piece per load instruction, two steps ahead of use, through a three-slot
-// register ring whose refills are issued between the products.  No LDS
-// image of Inv_t, no per-step split of it and no barrier for it remain on
-// the serial path, which is the row-wise update (entering state out, decay,
-// B_t in, split into bf16 hi / lo), one barrier, the matrix products and
-// another barrier.
+// 16-row block of the state); the rows of the state evolve independently.
+// The product is formed transposed, Inv_t^T x^T, with the operand tiles that
+// the inverse wrote (operand_tile_offset) as A-operands and the state as
+// B-operand of v_mfma_f32_16x16x32_bf16: a lane then receives four
+// consecutive columns of one state row, and output slices 2 w and 2 w + 1
+// are exactly the B-operand of k step w of the next product.  So wave w of
+// d_k / 32 owns the 32 state columns of k step w, in registers, all the way:
+// it adds B_t (and applies the decay) where the product leaves them, stores
+// the entering state, splits it and hands its operand (1 KB in each of two
+// planes) to the other waves through LDS, double buffered, with one barrier
+// per step (none at d_k = 32, one wave).  Each wave loads the tiles of its own
+// two output slices straight into registers, one contiguous 1 KB piece per
+// load instruction, two steps ahead of use: the two-slot ring refills a
+// piece's registers as soon as its products are issued.
+//
+// What bounds it: the serial step, operand reads after the barrier, 6 d_k / 32
+// products per wave, B_t and the split, at d_k = 128 about the time in which
+// a compute unit can load the 64 KB of tiles (with every load from two
+// frames only: 1.0 us a step at 16 heads, 1.2 with the real ones, 43 us for
+// 36 frames and 226 MB; 0.54 and 0.62 at d_k = 64).  With all of the state in
+// LDS and two barriers a step, passes were 3.5 us longer at 8 heads x 16
+// frames (16 steps: 20.5 -> 18.4 us), 2 at 16 x 36, 4 in the frozen rule's
+// map form; rings of three and four slots measured no faster (the loads are
+// not late).
 //
 // Products: the state operand x is split into hi = bf16(x) and
 // lo = bf16(x - hi) once per step, and hi*hi + hi*lo + lo*hi runs on the
@@ -31,93 +43,6 @@
 
 namespace vda {
 namespace {
-
-template <int DK>
-struct TiledDims {
-  static constexpr int NB = DK / 16;           // 16-column output slices
-  static constexpr int NBW = (NB + 3) / 4;     // slices per wave
-  static constexpr int KB = DK / 32;           // 32-wide k steps
-  static constexpr int XLD = DK + 4;           // fp32 state row stride (floats)
-  static constexpr int PLD = DK + 8;           // bf16 plane row stride (elements)
-  static constexpr int VW = DK >= 64 ? 4 : 2;  // floats per access in the row-wise phase
-  static constexpr int NG = DK / (16 * VW);    // accesses per thread in the row-wise phase
-};
-
-// One of this wave's tile loads: piece i of its NBW * KB * 2 pieces
-// (slice m = i / (2 KB), k step (i / 2) % KB, plane i % 2) of the tiles at
-// byte offset fbase of the tile buffer, into register slot t.
-template <int DK>
-__device__ __forceinline__ void load_tile_piece(
-    int i, u32x4 (&t)[TiledDims<DK>::NBW][TiledDims<DK>::KB][2],
-    const uint32_t (&toff)[TiledDims<DK>::NBW][TiledDims<DK>::KB][2],
-    __amdgpu_buffer_rsrc_t trsrc, uint32_t fbase) {
-  constexpr int KB = TiledDims<DK>::KB;
-  const int m = i / (2 * KB), ks = (i / 2) % KB, p = i % 2;
-  const uint32_t o = toff[m][ks][p];
-  t[m][ks][p] = __builtin_bit_cast(
-      u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                 trsrc, (int)(o == kOutOfRange ? kOutOfRange : fbase + o), 0, 0));
-}
-
-// Matrix-core phase of one step for wave w: xs_next = x Inv_t for this
-// wave's output slices nb = w, w + 4, ..., with x from the bf16 hi / lo
-// planes and Inv_t from the register tiles t[m][ks][plane].  Even and odd k
-// steps accumulate separately (two shorter dependency chains).  After each
-// k step's three products the wave issues two of the loads that fill
-// another ring slot (tn) with the tiles of a later step (byte offset
-// `next`), so the loads stream out between the products rather than in one
-// burst that would stall the wave at issue.  (Issuing the products of all
-// pairs term by term, with a separate accumulator per pair, measured slower:
-// the phase is bound by the loads' issue, not by the products' latency.)
-// The wave index is a run-time (scalar) value: one code path for all waves,
-// so the compiler's wait-count bookkeeping sees no merging branches and
-// keeps its waits partial.
-template <int DK>
-__device__ __forceinline__ void tiled_mfma_phase(
-    const uint16_t* __restrict__ xhi, const uint16_t* __restrict__ xlo,
-    float* __restrict__ xs_next, const u32x4 (&t)[TiledDims<DK>::NBW][TiledDims<DK>::KB][2],
-    u32x4 (&tn)[TiledDims<DK>::NBW][TiledDims<DK>::KB][2],
-    const uint32_t (&toff)[TiledDims<DK>::NBW][TiledDims<DK>::KB][2],
-    __amdgpu_buffer_rsrc_t trsrc, uint32_t next, int wave, int li, int lg) {
-  using D = TiledDims<DK>;
-  constexpr int NBW = D::NBW, KB = D::KB;
-  static_assert(D::NB % 4 == 0 || D::NB < 4, "slices are dealt out to four waves");
-  if (D::NB < 4 && wave >= D::NB) return;  // d_k = 32: two slices, waves 2 and 3 idle
-  // A-operand: row li of the block at k = 32 ks + 4 lg + e, 32 ks + 16 + 4 lg + e.
-  bf16x8 ahi[KB], alo[KB];
-#pragma unroll
-  for (int ks = 0; ks < KB; ++ks) {
-    const int o = li * D::PLD + 32 * ks + 4 * lg;
-    const u32x2 h0 = *reinterpret_cast<const u32x2*>(&xhi[o]);
-    const u32x2 h1 = *reinterpret_cast<const u32x2*>(&xhi[o + 16]);
-    const u32x2 l0 = *reinterpret_cast<const u32x2*>(&xlo[o]);
-    const u32x2 l1 = *reinterpret_cast<const u32x2*>(&xlo[o + 16]);
-    ahi[ks] = __builtin_bit_cast(bf16x8, u32x4{h0[0], h0[1], h1[0], h1[1]});
-    alo[ks] = __builtin_bit_cast(bf16x8, u32x4{l0[0], l0[1], l1[0], l1[1]});
-  }
-#pragma unroll
-  for (int m = 0; m < NBW; ++m) {
-    const int nb = wave + 4 * m;
-    floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-    for (int ks = 0; ks < KB; ++ks) {
-      const bf16x8 bhi = __builtin_bit_cast(bf16x8, t[m][ks][0]);
-      const bf16x8 blo = __builtin_bit_cast(bf16x8, t[m][ks][1]);
-      floatx4& a = acc[ks & 1];
-      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[ks], bhi, a, 0, 0, 0);
-      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[ks], blo, a, 0, 0, 0);
-      a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[ks], bhi, a, 0, 0, 0);
-      const int piece = 2 * (m * KB + ks);  // this wave's pieces in (slice, k step, plane) order
-      load_tile_piece<DK>(piece, tn, toff, trsrc, next);
-      load_tile_piece<DK>(piece + 1, tn, toff, trsrc, next);
-      __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);  // the three products
-      __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);  // then two loads of the refill
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      xs_next[(lg * 4 + i) * D::XLD + nb * 16 + li] = acc[0][i] + acc[1][i];
-  }
-}
 
 // Arguments of the tiled scan.  Frame scans: tiles = Inv_t tiles [H][F],
 // add = B [H][F][d_v][d_k].  Map scans (CHUNKED), x <- x M + add_scale J:
@@ -151,22 +76,24 @@ struct TiledScanArgs {
 // share a compute unit when there are more chains' row blocks than compute
 // units (e.g. 24 heads: 384 workgroups) instead of running in two rounds.
 template <int DK, bool DECAY, bool CHUNKED>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(2 * DK) __attribute__((amdgpu_waves_per_eu(2)))
 void scan_tiled_kernel(TiledScanArgs a) {
   static_assert(!(CHUNKED && DECAY), "chunk maps already hold the decay");
+  constexpr int KB = DK / 32;  // 32-wide k steps, and waves
+  constexpr uint32_t kPlane = DK * DK * 2;
+  constexpr int kRow = 36;     // floats per 32-column row in LDS
+  // The state's operand of a step: [step parity][k step][hi, lo][lane].
+  __shared__ u32x4 xop[KB > 1 ? 2 : 1][KB][2][64];
+  // Per wave: its 16 x 32 pieces of B_t and of the entering state on their
+  // way between memory order (eight lanes on one 128-byte run of a row) and
+  // the products' (a lane's row is lane % 16).  In memory the latter would
+  // be 16 bytes of a different row per lane, which the texture addresser
+  // takes four times as long for.
+  __shared__ __align__(16) float xb[KB][16 * kRow], xs[KB][16 * kRow];
   const int F = a.F, DV = a.DV, C = a.C;
-  const float* __restrict__ alpha = a.alpha;
-  const float* __restrict__ text_state = a.text_state;
-  const unsigned nwg = a.nwg;
-  using D = TiledDims<DK>;
-  constexpr int XLD = D::XLD, PLD = D::PLD, VW = D::VW, NG = D::NG;
-  constexpr int NBW = D::NBW, KB = D::KB;
-  __shared__ __align__(16) float xs[2][16 * XLD];
-  __shared__ __align__(16) uint16_t xsp[2][16 * PLD];   // bf16 hi / lo planes of the block
-  __shared__ __align__(16) float alds[DECAY ? DK : 4];  // alpha of the coming step
 
   const int nrb = DV / 16;
-  const unsigned L = xcd_grouped_id(blockIdx.x, nwg);
+  const unsigned L = xcd_grouped_id(blockIdx.x, a.nwg);
   const int rb = L % nrb;
   const unsigned chain = L / nrb;
   const int dir = chain & 1;
@@ -178,22 +105,24 @@ void scan_tiled_kernel(TiledScanArgs a) {
   const int li = lane & 15;
   const int lg = lane >> 4;
 
-  // Row-wise phase role: row pr of the block; access g covers columns
-  // pc + g * 16 * VW .. + VW - 1 (16 consecutive lanes on one contiguous run).
-  const int pr = tid >> 4;
-  const int pc = (tid & 15) * VW;
-
   const size_t mat_b = (size_t)DV * DK;  // one B / state matrix
-  // Initial state: S_T / 2 (rows of this block), or zero.
-  for (int i = tid; i < 16 * XLD; i += kThreads) {
-    const int r = i / XLD, c = i % XLD;
-    xs[0][i] = text_state != nullptr && c < DK
-                   ? 0.5f * text_state[(size_t)hb * mat_b + (size_t)(rb * 16 + r) * DK + c]
-                   : 0.f;
+  // This lane's state: row rb * 16 + li, columns col + 16 j + r (j < 2, r < 4).
+  const int col = 32 * wave + 4 * lg;
+  // In memory order: row mrow + 8 j, columns mcol .. mcol + 3 of the wave's 32.
+  const int mrow = lane >> 3, mcol = (lane & 7) * 4;
+  const uint32_t mem_off = (uint32_t)((rb * 16 + mrow) * DK + 32 * wave + mcol) * 4u;
+  float* const bm = &xb[wave][mrow * kRow + mcol];       // memory order, + 8 kRow j
+  const float* const bx = &xb[wave][li * kRow + 4 * lg]; // products' order, + 16 j
+  float* const sx = &xs[wave][li * kRow + 4 * lg];
+  const float* const sm = &xs[wave][mrow * kRow + mcol];
+  floatx4 x[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  if (a.text_state != nullptr) {  // S_T / 2
+    const float* ts = a.text_state + (size_t)hb * mat_b + (size_t)(rb * 16 + li) * DK + col;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) x[j] = 0.5f * *reinterpret_cast<const floatx4*>(ts + 16 * j);
   }
 
   float* Sout = dir == 0 ? a.S_fwd : a.S_rev;
-  const size_t row_off = (size_t)(rb * 16 + pr) * DK + pc;
   // Entering states of this head, [F][d_v][d_k]: a range-checked buffer.
   const __amdgpu_buffer_rsrc_t srsrc =
       make_rsrc(Sout + (size_t)hb * F * mat_b, (uint32_t)(F * mat_b * sizeof(float)));
@@ -205,26 +134,14 @@ void scan_tiled_kernel(TiledScanArgs a) {
   const __amdgpu_buffer_rsrc_t brsrc =
       make_rsrc(a.add + chain_mats * mat_b, (uint32_t)(nsteps * mat_b * sizeof(float)));
   const __amdgpu_buffer_rsrc_t arsrc =
-      make_rsrc(DECAY ? alpha + (size_t)hb * F * DK : a.add, DECAY ? (uint32_t)(F * DK * 4) : 0u);
+      make_rsrc(DECAY ? a.alpha + (size_t)hb * F * DK : a.add, DECAY ? (uint32_t)(F * DK * 4) : 0u);
   const __amdgpu_buffer_rsrc_t trsrc = make_rsrc(a.tiles + chain_mats * (DK * DK * 2),
                                                  (uint32_t)nsteps * (uint32_t)(DK * DK * 4));
 
-  // This wave's tile offsets within a frame (out of range for the slices of
-  // idle waves at d_k = 32).
-  uint32_t toff[NBW][KB][2];
-#pragma unroll
-  for (int m = 0; m < NBW; ++m) {
-    const int nb = wave + 4 * m;
-#pragma unroll
-    for (int ks = 0; ks < KB; ++ks)
-#pragma unroll
-      for (int p = 0; p < 2; ++p)
-        toff[m][ks][p] = nb < D::NB ? operand_tile_offset(DK, p, nb, ks, lane) : kOutOfRange;
-  }
-
   // Matrix of step `step` (frame or chunk in scan order), the index of its
   // additive term (chunks: the previous chunk's J, none before the first),
-  // and the frame whose entering state the step stores (-1: none).
+  // and the frame whose entering state the step stores (-1: none, for a
+  // padded step past the end).
   auto frame_of = [&](int step) { return dir == 0 ? step : nsteps - 1 - step; };
   auto add_of = [&](int step) {
     if constexpr (CHUNKED) return step >= 1 ? frame_of(step - 1) : -1;
@@ -239,152 +156,160 @@ void scan_tiled_kernel(TiledScanArgs a) {
     return frame_of(step);
   };
 
-  // Three-slot register ring, as separately named arrays (compile-time
-  // indices only): step s reads slot s % 3 while the loads of step s + 2
-  // fill slot (s + 2) % 3, which step s - 1 has released.
-  u32x4 t0[NBW][KB][2], t1[NBW][KB][2], t2[NBW][KB][2];
-  float bs0[NG][VW], bs1[NG][VW], bs2[NG][VW];
-  u32x4 al0, al1, al2;  // alpha_t, columns 4 tid .. 4 tid + 3 (threads tid < DK / 4)
-  auto load_add = [&](int step, float (&bb)[NG][VW], u32x4& al) {
-    const int frame = frame_of(step);
+  // Two-slot register ring, as separately named arrays (compile-time indices
+  // only): step s uses slot s % 2, whose registers take step s + 2 (past the
+  // end: a clamped, unused step, so no branch hides the loads from the
+  // wait-count bookkeeping).
+  struct Slot {
+    u32x4 t[2][KB][2];  // tiles of slices 2 wave + j: [j][k step][plane]
+    floatx4 b[2];       // B_t (J), memory order
+    floatx4 al[2];      // alpha_t
+  };
+  Slot s0, s1;
+  auto load_add = [&](int step, Slot& s) {
     const int ai = add_of(step);
-    // B rows first (they are needed earlier in the step than the tiles),
-    // and everything through buffer loads, which the compiler keeps in
-    // program order.
+    const uint32_t off = (uint32_t)ai * (uint32_t)(mat_b * 4u) + mem_off;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const uint32_t off =
-          ai >= 0 ? (uint32_t)(((size_t)ai * mat_b + row_off + g * 16 * VW) * 4u) : kOutOfRange;
-      if constexpr (VW == 4) {
-        const u32x4 x =
-            __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, (int)off, 0, 0));
-#pragma unroll
-        for (int v = 0; v < 4; ++v) bb[g][v] = __uint_as_float(x[v]);
-      } else {
-        const u32x2 x =
-            __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)off, 0, 0));
-        bb[g][0] = __uint_as_float(x[0]);
-        bb[g][1] = __uint_as_float(x[1]);
-      }
-    }
+    for (int j = 0; j < 2; ++j)
+      s.b[j] = __builtin_bit_cast(
+          floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                       brsrc, (int)(ai >= 0 ? off + (uint32_t)(8 * DK * 4 * j) : kOutOfRange), 0, 0));
     if constexpr (DECAY) {
-      const uint32_t off = tid < DK / 4 ? (uint32_t)(frame * DK + 4 * tid) * 4u : kOutOfRange;
-      al = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(arsrc, (int)off, 0, 0));
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        s.al[j] = __builtin_bit_cast(
+            floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                         arsrc, (int)((uint32_t)(frame_of(step) * DK + col + 16 * j) * 4u), 0, 0));
     }
+  };
+  const uint32_t toff = operand_tile_offset(DK, 0, 2 * wave, 0, lane);
+  auto load_piece = [&](uint32_t fbase, Slot& s, int j, int ks) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+      s.t[j][ks][p] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                     trsrc, (int)(toff + (uint32_t)(j * KB + ks) * 1024u + (uint32_t)p * kPlane),
+                     (int)fbase, 0));
   };
   auto tile_base = [&](int step) { return (uint32_t)frame_of(step) * (uint32_t)(DK * DK * 4); };
-  auto load_tiles = [&](int step, u32x4 (&t)[NBW][KB][2]) {
-    const uint32_t fbase = tile_base(step);
+
+  // B of the coming step in the products' order, by way of this wave's LDS
+  // (a wave's LDS operations run in order).
+  floatx4 bn[2];
+  auto turn_b = [&](const Slot& s) {
 #pragma unroll
-    for (int m = 0; m < NBW; ++m)
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<floatx4*>(bm + 8 * kRow * j) = s.b[j];
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int ks = 0; ks < KB; ++ks)
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          const uint32_t o = toff[m][ks][p];
-          t[m][ks][p] = __builtin_bit_cast(
-              u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                         trsrc, (int)(o == kOutOfRange ? kOutOfRange : fbase + o), 0, 0));
-        }
+    for (int j = 0; j < 2; ++j) bn[j] = *reinterpret_cast<const floatx4*>(bx + 16 * j);
+    __builtin_amdgcn_wave_barrier();
   };
 
-  int cur = 0;
-  // Step `step` on slot (t, bb); (tn, bn, aln) is the slot the step fills
-  // with step + 2 (B and alpha at its start, the tiles between its
-  // products; past the end: a clamped, unused step), always, so no
-  // branch hides the loads from the wait-count bookkeeping; al_next is the
-  // alpha of step + 1, loaded a step ago.
-  auto step_body = [&](int step, const u32x4 (&t)[NBW][KB][2], const float (&bb)[NG][VW],
-                       const u32x4& al_next, u32x4 (&tn)[NBW][KB][2], float (&bn)[NG][VW],
-                       u32x4& aln) {
-    // Frame whose entering state this step stores (-1 for a padded step
-    // past the end: the stores go out of the buffer's range).
-    const int sf = store_frame(step);
-    lds_barrier();  // xs[cur] holds the entering state; last step's plane reads are done
-    const int refill = min(step + 2, nsteps - 1);
-    const uint32_t next = tile_base(refill);
-    load_add(refill, bn, aln);
-    {
+  // Step `step` on slot s; o is the other slot, the coming step's.
+  auto step_body = [&](int step, int par, Slot& s, const Slot& o) {
+    floatx4 u[2];
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const uint32_t off =
-            sf >= 0 ? (uint32_t)(((size_t)sf * mat_b + row_off + g * 16 * VW) * 4u) : kOutOfRange;
-        const int xo = pr * XLD + pc + g * 16 * VW;
-        float v[VW];
-        if constexpr (VW == 4) {
-          const floatx4 xv = reinterpret_cast<const floatx4*>(xs[cur])[xo / 4];
+    for (int j = 0; j < 2; ++j) {
+      if constexpr (CHUNKED) {  // J of the previous chunk, after its product
 #pragma unroll
-          for (int c = 0; c < 4; ++c) v[c] = xv[c];
-        } else {
-          const float2 xv = *reinterpret_cast<const float2*>(&xs[cur][xo]);
-          v[0] = xv.x;
-          v[1] = xv.y;
-        }
-        if constexpr (CHUNKED) {  // J of the previous chunk, after its product
-#pragma unroll
-          for (int c = 0; c < VW; ++c) v[c] = fmaf(bb[g][c], a.add_scale, v[c]);
-        }
-        if constexpr (VW == 4)
-          store_b128(srsrc, off,
-                     u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
-                           __float_as_uint(v[3])});
-        else
-          store_b64(srsrc, off, make_uint2(__float_as_uint(v[0]), __float_as_uint(v[1])));
-        if constexpr (DECAY) {
-#pragma unroll
-          for (int c = 0; c < VW; ++c) v[c] *= alds[pc + g * 16 * VW + c];
-        }
-        if constexpr (!CHUNKED) {  // B of this frame, before its product
-#pragma unroll
-          for (int c = 0; c < VW; ++c) v[c] += bb[g][c];
-        }
-        // The product's A-operand, split once here into bf16 hi and lo.
-        uint32_t hw[VW / 2], lw[VW / 2];
-#pragma unroll
-        for (int c = 0; c < VW; c += 2) {
-          const uint32_t h = pack_bf16x2(v[c], v[c + 1]);
-          hw[c / 2] = h;
-          lw[c / 2] = pack_bf16x2(v[c] - bf16_lo(h), v[c + 1] - bf16_hi(h));
-        }
-        const int po = pr * PLD + pc + g * 16 * VW;
-        if constexpr (VW == 4) {
-          *reinterpret_cast<u32x2*>(&xsp[0][po]) = u32x2{hw[0], hw[1]};
-          *reinterpret_cast<u32x2*>(&xsp[1][po]) = u32x2{lw[0], lw[1]};
-        } else {
-          *reinterpret_cast<uint32_t*>(&xsp[0][po]) = hw[0];
-          *reinterpret_cast<uint32_t*>(&xsp[1][po]) = lw[0];
-        }
+        for (int r = 0; r < 4; ++r) x[j][r] = fmaf(bn[j][r], a.add_scale, x[j][r]);
+        u[j] = x[j];
+      } else {  // B of this frame, before its product
+        u[j] = DECAY ? x[j] * s.al[j] + bn[j] : x[j] + bn[j];
       }
     }
-    lds_barrier();
-    // alpha of the next step, read by its row-wise phase (after the next
-    // barrier); this step's reads of alds are complete.
-    if constexpr (DECAY) {
-      if (tid < DK / 4) reinterpret_cast<u32x4*>(alds)[tid] = al_next;
+    // The product's B-operand of k step `wave`, split into bf16 hi and lo.
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float v0 = u[q / 2][2 * (q % 2)], v1 = u[q / 2][2 * (q % 2) + 1];
+      h[q] = pack_bf16x2(v0, v1);
+      l[q] = pack_bf16x2(v0 - bf16_lo(h[q]), v1 - bf16_hi(h[q]));
     }
-    // The products, with the second half of the refill between them.
-    tiled_mfma_phase<DK>(xsp[0], xsp[1], xs[cur ^ 1], t, tn, toff, trsrc, next, wave, li, lg);
-    cur ^= 1;
+    bf16x8 xh[KB], xl[KB];
+    if constexpr (KB > 1) {
+      xop[par][wave][0][lane] = u32x4{h[0], h[1], h[2], h[3]};
+      xop[par][wave][1][lane] = u32x4{l[0], l[1], l[2], l[3]};
+    }
+    // The entering state, on its way to memory.
+#pragma unroll
+    for (int j = 0; j < 2; ++j) *reinterpret_cast<floatx4*>(sx + 16 * j) = x[j];
+    if constexpr (KB > 1) {
+      lds_barrier();  // the state's operand is complete
+#pragma unroll
+      for (int ks = 0; ks < KB; ++ks) {
+        xh[ks] = __builtin_bit_cast(bf16x8, xop[par][ks][0][lane]);
+        xl[ks] = __builtin_bit_cast(bf16x8, xop[par][ks][1][lane]);
+      }
+    } else {
+      xh[0] = __builtin_bit_cast(bf16x8, u32x4{h[0], h[1], h[2], h[3]});
+      xl[0] = __builtin_bit_cast(bf16x8, u32x4{l[0], l[1], l[2], l[3]});
+    }
+    const int refill = min(step + 2, nsteps - 1);
+    const uint32_t next = tile_base(refill);
+    __builtin_amdgcn_wave_barrier();
+    floatx4 y[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) y[j] = *reinterpret_cast<const floatx4*>(sm + 8 * kRow * j);
+    load_add(refill, s);
+    turn_b(o);
+    const int sf = store_frame(step);
+    const uint32_t soff = (uint32_t)sf * (uint32_t)(mat_b * 4u) + mem_off;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      store_b128(srsrc, sf >= 0 ? soff + (uint32_t)(8 * DK * 4 * j) : kOutOfRange,
+                 __builtin_bit_cast(u32x4, y[j]));
+    // Even and odd k steps accumulate separately, and the two slices in turn:
+    // four independent chains.  After a k step's products its tiles are
+    // refilled.
+    floatx4 acc[2][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) acc[j][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KB; ++ks) {
+      const int e = ks & 1;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, s.t[j][ks][0]), xl[ks], acc[j][e], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, s.t[j][ks][1]), xh[ks], acc[j][e], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, s.t[j][ks][0]), xh[ks], acc[j][e], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) load_piece(next, s, j, ks);
+      __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);  // the six products
+      __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);  // then the refill's four loads
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) x[j] = KB > 1 ? acc[j][0] + acc[j][1] : acc[j][0];
   };
 
   // Issue the ring in slot order (pinned against rescheduling) so slot 0 is
   // the oldest load on loop entry.
-  load_add(0, bs0, al0);
-  load_tiles(0, t0);
-  __builtin_amdgcn_sched_barrier(0);
-  load_add(min(1, nsteps - 1), bs1, al1);
-  load_tiles(min(1, nsteps - 1), t1);
-  __builtin_amdgcn_sched_barrier(0);
-  if constexpr (DECAY) {  // alpha of step 0
-    if (tid < DK / 4) reinterpret_cast<u32x4*>(alds)[tid] = al0;
-  }
-  // The step count is padded to a multiple of three; a padded step
+  auto fill = [&](int step, Slot& s) {
+    load_add(step, s);
+#pragma unroll
+    for (int ks = 0; ks < KB; ++ks)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) load_piece(tile_base(step), s, j, ks);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  fill(0, s0);
+  fill(min(1, nsteps - 1), s1);
+  turn_b(s0);
+  // The step count is padded to a multiple of two; a padded step
   // (step >= nsteps) reads a clamped matrix and stores nothing, so the loop
   // body has no early exit.
-  for (int step0 = 0; step0 < nsteps; step0 += 3) {
-    step_body(step0, t0, bs0, al1, t2, bs2, al2);
-    step_body(step0 + 1, t1, bs1, al2, t0, bs0, al0);
-    step_body(step0 + 2, t2, bs2, al0, t1, bs1, al1);
+  for (int step = 0; step < nsteps; step += 2) {
+    step_body(step, 0, s0, s1);
+    step_body(step + 1, KB > 1 ? 1 : 0, s1, s0);
   }
 }
 
@@ -498,7 +423,7 @@ void frozen_tiles_kernel(float* __restrict__ A, const float* __restrict__ alpha,
 template <int DK, bool DECAY, bool CHUNKED>
 hipError_t launch_tiled_k(TiledScanArgs a, int H, hipStream_t stream) {
   a.nwg = (unsigned)H * 2u * (unsigned)(a.DV / 16);
-  hipLaunchKernelGGL((scan_tiled_kernel<DK, DECAY, CHUNKED>), dim3(a.nwg), dim3(kThreads), 0,
+  hipLaunchKernelGGL((scan_tiled_kernel<DK, DECAY, CHUNKED>), dim3(a.nwg), dim3(2 * DK), 0,
                      stream, a);
   return hipGetLastError();
 }
