@@ -216,26 +216,44 @@ int stats_blocks_per_cu(int dev, int d_k, int d_v) {
 // rounds of `slots` frames; when the last round is partial, its frames are
 // split into token ranges so that the end of the launch keeps more compute
 // units busy.  Each extra range costs one partial A_t, B_t written here and
-// read back by the inverse step, which is why the split is kept small and
-// limited to the partial round.
-// bf16 storage: the step streams, so a round is every resident workgroup
-// (two per compute unit), and a range has at least 256 tokens, at most four
-// per frame.  fp32 storage: the step is bound by the fp32 matrix rate, which
-// the workgroups of a compute unit share, so a round is one frame per compute
+// read back by the inverse step, which is why the split is limited to the
+// partial round.
+// bf16 storage: the step streams, and a round is every resident workgroup
+// (two per compute unit).  Of one to four ranges, of at least 256 tokens and
+// resident together (300 frames of 2000 tokens: 191 us a pass, 199 in 600
+// ranges), the cheapest by this model, in ns at d_k = d_v = 128: the compute unit with
+// the most ranges takes 32 a token if it has one and 24 a token of all of
+// them if it has more, and a partial matrix pair 40 of the whole device
+// (scaled with the bytes of a token and of a partial).  It was fitted to
+// whole passes over 128 frames (2 and 4 ranges: 1024 tokens 75.7 and 82.5 us,
+// 4032 tokens 158.6 and 153.3), 148 after a full round (2000 tokens, 1, 2 and
+// 3 ranges: 369, 357, 354) and 192 of d_k = 64 (2000 tokens, 1 and 4 ranges:
+// 92.4 and 80.2).
+// fp32 storage: the step is bound by the fp32 matrix rate, which the
+// workgroups of a compute unit share, so a round is one frame per compute
 // unit (84 frames of 1560 tokens: 3 ranges, 252 workgroups; 4 ranges left
 // 80 compute units with two of 336); a token takes about 0.09 us of a compute
 // unit and a further partial about 1 us of the inverse, so up to eight
 // ranges of at least 128 tokens.
 vda::SplitPlan default_plan(int dev, int F, int N, int H, int d_k, int d_v, bool is_f32) {
-  const int max_splits = is_f32 ? 8 : 4, min_tokens = is_f32 ? 128 : 256;
   const long long count = (long long)H * F;
-  const long long slots =
-      (is_f32 ? 1LL : (long long)stats_blocks_per_cu(dev, d_k, d_v)) * current_device_cus();
+  const long long cus = current_device_cus();
+  const long long slots = is_f32 ? cus : cus * stats_blocks_per_cu(dev, d_k, d_v);
   const long long rem = count % slots;
   if (rem == 0) return vda::SplitPlan{0, 1};
-  long long k = slots / rem;
-  if (k > max_splits) k = max_splits;
-  if (k > N / min_tokens) k = N / min_tokens;
+  long long k = 1;
+  if (is_f32) {
+    k = std::min({slots / rem, 8LL, (long long)N / 128});
+  } else {
+    const double token = (d_k + d_v) / 256.0, partial = d_k * (d_v + 0.6 * d_k) / 26214.4;
+    double best = 0.0;
+    for (int c = 1; c <= 4 && rem * c <= slots && (c == 1 || N / c >= 256); ++c) {
+      const long long most = (rem * c + cus - 1) / cus;
+      const double cost = (double)most * ((N + c - 1) / c) * (most == 1 ? 32.0 : 24.0) * token +
+                          (double)((c - 1) * rem) * 40.0 * partial;
+      if (c == 1 || cost < best) best = cost, k = c;
+    }
+  }
   if (k < 2) return vda::SplitPlan{0, 1};
   return vda::SplitPlan{(int)rem, (int)k};
 }
