@@ -24,7 +24,14 @@
 // wave for K) and stored.  Every input is read from memory once per tile
 // that needs it (tiles sharing a halo run on one XCD, so the re-reads hit
 // its L2) and every output is written once.  The work is bound by the fp32
-// FMAs (25 + 5 per output channel).
+// FMAs (25 + 5 per output channel): 480 of ~700 vector instructions per wave
+// and frame, and two quarter-rate ones per output.  At 16 heads x 36 frames x
+// 48 x 80 tokens, d = 128, K takes 430 us and V 394 in a trace; 461 and 425
+// with ~760 instructions (log2(e) multiplied in SiLU instead of once into the
+// taps, sums cleared instead of set by the first tap, addresses of whole
+// clips).  The filter on 4 x 4 x 4 matrix products with the taps in three
+// bf16 parts issues half the instructions and takes 491 and 413 us: the small
+// products and the vector instructions share the issue port.
 //
 // Q kernel: each wave normalises four tokens of one head per pass, a lane
 // holding eight channels (16-byte loads and stores), with the reduction
@@ -42,10 +49,15 @@ constexpr int kPTY = 8, kPTX = 8;                    // output tile (rows = wave
 constexpr int kPHY = kPTY + 4, kPHX = kPTX + 4;      // with the 2-token halo
 static_assert(kPTX == 8, "the L2 reduction sums eight tokens per wave row");
 
-// SiLU with the hardware reciprocal (1 ulp): for x -> -inf, exp(-x)
+// The temporal taps carry a factor log2(e), so a convolution's value arrives
+// as z = x log2(e), ready for the hardware's base-2 exponential.
+constexpr float kLog2e = 1.44269504088896340736f;
+
+// SiLU x / (1 + exp(-x)) of x = z / log2(e), with the hardware reciprocal (1
+// ulp): z / (log2(e) + log2(e) 2^-z).  For z -> -inf the exponential
 // overflows to inf and the result is -0, the limit.
-__device__ __forceinline__ float silu(float x) {
-  return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x));
+__device__ __forceinline__ float silu_log2e(float z) {
+  return z * __builtin_amdgcn_rcpf(fmaf(__builtin_amdgcn_exp2f(-z), kLog2e, kLog2e));
 }
 
 #define VDA_DPP(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
@@ -134,7 +146,7 @@ void prep_conv_kernel(PrepConvArgs a) {
 #pragma unroll
     for (int i = 0; i < 25; ++i) wsp[c][i] = a.ws[(size_t)ch * 25 + i];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) wtp[c][i] = a.wt[(size_t)ch * 5 + i];
+    for (int i = 0; i < 5; ++i) wtp[c][i] = a.wt[(size_t)ch * 5 + i] * kLog2e;
   }
 
   // One input frame's haloed tile: chunk q (16 bytes) of the tile is piece
@@ -144,8 +156,9 @@ void prep_conv_kernel(PrepConvArgs a) {
   // and written to LDS as eight fp32 values after the current frame's
   // filters.
   constexpr int CPT = (CHUNKS + kConvThreads - 1) / kConvThreads;  // chunks per thread
-  const __amdgpu_buffer_rsrc_t irsrc =
-      make_rsrc(a.in + (size_t)b * F * N * C, (uint32_t)((size_t)F * N * C * 2));
+  // (The buffer range is one frame, so a frame costs no address arithmetic
+  // per chunk and off-grid chunks stay out of range.)
+  const uint16_t* ibase = a.in + (size_t)b * F * N * C;
   uint32_t coff[CPT];  // byte offset within a frame, or out of range
 #pragma unroll
   for (int i = 0; i < CPT; ++i) {
@@ -158,12 +171,11 @@ void prep_conv_kernel(PrepConvArgs a) {
   }
   u32x4 stage[CPT];
   auto load_frame = [&](int f) {
-    const uint32_t fb = (uint32_t)f * (uint32_t)(N * C * 2);
+    const __amdgpu_buffer_rsrc_t irsrc = make_rsrc(ibase + (size_t)f * N * C, (uint32_t)N * (uint32_t)C * 2u);
 #pragma unroll
     for (int i = 0; i < CPT; ++i)
       stage[i] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                     irsrc, (int)(coff[i] == kOutOfRange ? kOutOfRange : fb + coff[i]), 0, 0));
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(irsrc, (int)coff[i], 0, 0));
   };
   auto store_frame = [&](float* dst) {
 #pragma unroll
@@ -181,7 +193,8 @@ void prep_conv_kernel(PrepConvArgs a) {
   // Output tokens of this wave: grid row y0 + wave, columns x0 .. x0 + 7.
   const int oy = y0 + wave;
   uint16_t* obase = a.out + ((size_t)(b * H + h) * F) * N * D;
-  const __amdgpu_buffer_rsrc_t orsrc = make_rsrc(obase, (uint32_t)((size_t)F * N * D * 2));
+  // Byte offset of the row's first token and the lane's channels in a frame.
+  const uint32_t ooff = (uint32_t)(((oy * gw + x0) * D + lane * CPL) * 2);
   // Running sums of the pending output frames: output frame o lives in
   // slot o % 5.  Slots start at zero (outputs 0 and 1 take their first
   // terms by accumulation); the slot of output f + 2 is set, not added to,
@@ -201,11 +214,7 @@ void prep_conv_kernel(PrepConvArgs a) {
     constexpr int P = decltype(phase)::value;
     const float* tb = tile[f & 1];
     if (f < F) {
-      float sp[kPTX][CPL];
-#pragma unroll
-      for (int x = 0; x < kPTX; ++x)
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) sp[x][c] = 0.f;
+      float sp[kPTX][CPL];  // (set by the first tap)
 #pragma unroll
       for (int dy = 0; dy < 5; ++dy) {
         float in[kPHX][CPL];
@@ -225,7 +234,9 @@ void prep_conv_kernel(PrepConvArgs a) {
 #pragma unroll
           for (int x = 0; x < kPTX; ++x)
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) sp[x][c] = fmaf(wsp[c][dy * 5 + dx], in[x + dx][c], sp[x][c]);
+            for (int c = 0; c < CPL; ++c)
+              sp[x][c] = dy == 0 && dx == 0 ? wsp[c][0] * in[x][c]
+                                            : fmaf(wsp[c][dy * 5 + dx], in[x + dx][c], sp[x][c]);
       }
 #pragma unroll
       for (int x = 0; x < kPTX; ++x)
@@ -246,7 +257,7 @@ void prep_conv_kernel(PrepConvArgs a) {
         scale[x] = 0.f;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-          y[x][c] = silu(ring[OS][x][c]);
+          y[x][c] = silu_log2e(ring[OS][x][c]);
           scale[x] = fmaf(y[x][c], y[x][c], scale[x]);
         }
       }
@@ -261,12 +272,14 @@ void prep_conv_kernel(PrepConvArgs a) {
         for (int x = 0; x < kPTX; ++x) scale[x] = 1.0f;
       }
       if (oy < gh) {
+        const __amdgpu_buffer_rsrc_t orsrc =
+            make_rsrc(obase + (size_t)o * N * D, (uint32_t)N * (uint32_t)(D * 2));
 #pragma unroll
         for (int x = 0; x < kPTX; ++x) {
           if (x0 + x < gw) {
             // Streamed stores (sc0 | nt | sc1): the features are read by the
             // next kernels, not kept dirty in the caches for them to evict.
-            const uint32_t off = (uint32_t)((((size_t)o * N + oy * gw + x0 + x) * D + lane * CPL) * 2);
+            const uint32_t off = ooff + (uint32_t)(x * D * 2);
             if constexpr (CPL == 2)
               __builtin_amdgcn_raw_buffer_store_b32(pack_bf16x2(y[x][0] * scale[x], y[x][1] * scale[x]),
                                                     orsrc, (int)off, 0, 1 | 2 | 16);
