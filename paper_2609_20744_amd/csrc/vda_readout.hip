@@ -75,7 +75,11 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
   constexpr int KB = DK / 32;  // 32-wide k steps
   constexpr int OLD = DV + 8;  // bf16 row stride of the output staging tiles
   __shared__ __align__(16) uint16_t st[DV * SLD];
-  __shared__ __align__(16) uint16_t otile[4 * 16 * OLD];  // one 16-token tile per wave
+  // One 16-token output tile per wave: bf16, or with an output gate per token
+  // fp32, so that the gate is applied where whole rows are stored and its own
+  // rows are read in the stores' layout.
+  constexpr int GLD = DV + 4;  // fp32 row stride
+  __shared__ __align__(16) uint16_t otile[TOKGATE ? 4 * 16 * GLD * 2 : 4 * 16 * OLD];
 
   // The chunks of one frame read the same two states: keep them on one XCD.
   const unsigned L = xcd_grouped_id(blockIdx.x, nwg);
@@ -161,11 +165,23 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
     for (int kb = 0; kb < KB; ++kb)
       qv[kb] = *reinterpret_cast<const uint4*>(qbase + (size_t)row * qrs + kb * 32 + lg * 8);
   };
-  // TOKGATE: a group's output gate, four channels per lane and row block in
-  // the accumulators' layout, loaded after the group's products (rows past
-  // the frame read as zero).
+  // TOKGATE: the output gate of the same groups, whole rows in the stores'
+  // layout (rows past the frame read as zero); read once, so streamed (nt).
+  constexpr int CPR = DV / 8;     // 16-byte chunks per token row
+  constexpr int RPI = 64 / CPR;   // token rows per store instruction
   const __amdgpu_buffer_rsrc_t grsrc =
       make_rsrc(TOKGATE ? gtok + (size_t)fh * N * DV : Q, TOKGATE ? (uint32_t)N * DV * 2u : 0u);
+  u32x4 gr[TOKGATE ? kQ : 1][TOKGATE ? 16 / RPI : 1];
+  auto load_gate = [&](int ng, u32x4 (&gv)[TOKGATE ? 16 / RPI : 1]) {
+    if constexpr (TOKGATE) {
+#pragma unroll
+      for (int r = 0; r < 16 / RPI; ++r)
+        gv[r] = __builtin_bit_cast(
+            u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                       grsrc, (int)(((uint32_t)(ng + r * RPI + lane / CPR) * DV + lane % CPR * 8) * 2u),
+                       0, 2));
+    }
+  };
   const __amdgpu_buffer_rsrc_t orsrc =
       make_rsrc(obase, ((uint32_t)(N - 1) * ors + (uint32_t)dvw) * 2u);
 
@@ -176,6 +192,7 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
 #pragma unroll
   for (int d = 0; d < kQ; ++d) {
     load_q(n_first + S * d, qr[d]);
+    if constexpr (TOKGATE) load_gate(n_first + S * d, gr[d]);
     __builtin_amdgcn_sched_barrier(0);
   }
   for (int n0 = n_first; n0 < N; n0 += S * kQ) {
@@ -227,14 +244,6 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
         }
       }
       load_q(ng + S * kQ, qr[d]);
-      u32x2 gnow[MB];  // this group's gate, in flight during the norm's reduction
-      if constexpr (TOKGATE) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-          gnow[mb] = __builtin_bit_cast(
-              u32x2, __builtin_amdgcn_raw_buffer_load_b64(
-                         grsrc, (int)(((uint32_t)(ng + li) * DV + mb * 16 + 4 * lg) * 2u), 0, 0));
-      }
       // lane holds o[token ng + li][mb*16 + 4*lg + i]
       float ss = 0.f;
 #pragma unroll
@@ -250,29 +259,40 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
       // bf16) go through this wave's LDS tile, then each store instruction
       // writes 64 / (DV / 8) consecutive token rows, one contiguous run of
       // up to 1 KB.
-      uint16_t* tile = otile + wave * (16 * OLD);
+      if constexpr (TOKGATE) {
+        float* tile = reinterpret_cast<float*>(otile) + wave * (16 * GLD);
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        float sc[4] = {scale, scale, scale, scale};
-        if constexpr (TOKGATE) {
-          sc[0] *= bf16_lo(gnow[mb][0]);
-          sc[1] *= bf16_hi(gnow[mb][0]);
-          sc[2] *= bf16_lo(gnow[mb][1]);
-          sc[3] *= bf16_hi(gnow[mb][1]);
+        for (int mb = 0; mb < MB; ++mb)
+          *reinterpret_cast<floatx4*>(&tile[li * GLD + mb * 16 + 4 * lg]) = acc[mb] * scale;
+#pragma unroll
+        for (int r = 0; r < 16 / RPI; ++r) {
+          const int tok = r * RPI + lane / CPR, ch = lane % CPR;
+          const floatx4 y0 = *reinterpret_cast<const floatx4*>(&tile[tok * GLD + ch * 8]);
+          const floatx4 y1 = *reinterpret_cast<const floatx4*>(&tile[tok * GLD + ch * 8 + 4]);
+          const u32x4 gw = gr[d][r];
+          const u32x4 v = {pack_bf16x2(y0[0] * bf16_lo(gw[0]), y0[1] * bf16_hi(gw[0])),
+                           pack_bf16x2(y0[2] * bf16_lo(gw[1]), y0[3] * bf16_hi(gw[1])),
+                           pack_bf16x2(y1[0] * bf16_lo(gw[2]), y1[1] * bf16_hi(gw[2])),
+                           pack_bf16x2(y1[2] * bf16_lo(gw[3]), y1[3] * bf16_hi(gw[3]))};
+          store_b128_stream(orsrc, !GENOUT || ch * 8 < dvw ? ((uint32_t)(ng + tok) * ors + ch * 8) * 2u
+                                                          : kOutOfRange, v);
         }
-        *reinterpret_cast<uint2*>(&tile[li * OLD + mb * 16 + 4 * lg]) =
-            make_uint2(pack_bf16x2(acc[mb][0] * sc[0], acc[mb][1] * sc[1]),
-                       pack_bf16x2(acc[mb][2] * sc[2], acc[mb][3] * sc[3]));
-      }
-      constexpr int CPR = DV / 8;     // 16-byte chunks per token row
-      constexpr int RPI = 64 / CPR;   // token rows per store instruction
+        load_gate(ng + S * kQ, gr[d]);
+      } else {
+        uint16_t* tile = otile + wave * (16 * OLD);
 #pragma unroll
-      for (int r0 = 0; r0 < 16; r0 += RPI) {
-        const int tok = r0 + lane / CPR, ch = lane % CPR;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(&tile[tok * OLD + ch * 8]);
-        // Channels past dvo (zero padding of a narrow head) are not stored.
-        store_b128_stream(orsrc, !GENOUT || ch * 8 < dvw ? ((uint32_t)(ng + tok) * ors + ch * 8) * 2u
-                                                        : kOutOfRange, v);
+        for (int mb = 0; mb < MB; ++mb)
+          *reinterpret_cast<uint2*>(&tile[li * OLD + mb * 16 + 4 * lg]) =
+              make_uint2(pack_bf16x2(acc[mb][0] * scale, acc[mb][1] * scale),
+                         pack_bf16x2(acc[mb][2] * scale, acc[mb][3] * scale));
+#pragma unroll
+        for (int r0 = 0; r0 < 16; r0 += RPI) {
+          const int tok = r0 + lane / CPR, ch = lane % CPR;
+          const u32x4 v = *reinterpret_cast<const u32x4*>(&tile[tok * OLD + ch * 8]);
+          // Channels past dvo (zero padding of a narrow head) are not stored.
+          store_b128_stream(orsrc, !GENOUT || ch * 8 < dvw ? ((uint32_t)(ng + tok) * ors + ch * 8) * 2u
+                                                          : kOutOfRange, v);
+        }
       }
     }
   }
