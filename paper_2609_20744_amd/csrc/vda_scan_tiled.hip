@@ -206,7 +206,7 @@ void scan_tiled_kernel(TiledScanArgs a) {
   };
 
   // Step `step` on slot s; o is the other slot, the coming step's.
-  auto step_body = [&](int step, int par, Slot& s, const Slot& o) {
+  auto step_body = [&](int step, int par, Slot& s, Slot& o) {
     floatx4 u[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -230,6 +230,16 @@ void scan_tiled_kernel(TiledScanArgs a) {
     if constexpr (KB > 1) {
       xop[par][wave][0][lane] = u32x4{h[0], h[1], h[2], h[3]};
       xop[par][wave][1][lane] = u32x4{l[0], l[1], l[2], l[3]};
+    }
+    // The later k steps' tiles of the step before, refilled here rather than
+    // behind its products, so that the loads spread over the whole step (at
+    // step 0: the same tiles again).
+    if constexpr (KB > 1) {
+      const uint32_t late = tile_base(min(step + 1, nsteps - 1));
+#pragma unroll
+      for (int ks = KB / 2; ks < KB; ++ks)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) load_piece(late, o, j, ks);
     }
     // The entering state, on its way to memory.
 #pragma unroll
@@ -282,10 +292,13 @@ void scan_tiled_kernel(TiledScanArgs a) {
       for (int j = 0; j < 2; ++j)
         acc[j][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
             __builtin_bit_cast(bf16x8, s.t[j][ks][0]), xh[ks], acc[j][e], 0, 0, 0);
+      if (KB == 1 || ks < KB / 2) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) load_piece(next, s, j, ks);
+        for (int j = 0; j < 2; ++j) load_piece(next, s, j, ks);
+      }
       __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);  // the six products
-      __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);  // then the refill's four loads
+      if (KB == 1 || ks < KB / 2)
+        __builtin_amdgcn_sched_group_barrier(0x020, 4, 0);  // then the refill's four loads
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) x[j] = KB > 1 ? acc[j][0] + acc[j][1] : acc[j][0];
