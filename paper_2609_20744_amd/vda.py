@@ -118,18 +118,34 @@ def _check(status: int, where: str) -> None:
 # ----------------------------------------------------------------------------
 
 def _torch():
-    import torch
     return torch
 
 
+# The raw handle of a device's current stream without a Stream object around
+# it (about 1 us a call); the public spelling where torch lacks it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(device, stream=None) -> int:
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return int(torch.cuda.current_stream(device).cuda_stream)
+
+
+def _call(fn, device, *args) -> int:
+    """fn(*args) with `device` current; switching is left out where it is."""
+    if device.index == torch.cuda.current_device():
+        return fn(*args)
+    with torch.cuda.device(device):
+        return fn(*args)
 
 
 def _require(t, name, dtype, device):
-    torch = _torch()
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.device == device
+            and t.is_contiguous()):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device != device:
@@ -209,9 +225,8 @@ def forward(q, k, v, beta, gate, out=None, stream=None, alpha=None, text_state=N
     if alpha is None and text_state is None and window is None and rule == "joint" and \
             gate_tokens is None and not oh and not qh:
         fn = lib.vda_forward if dt == torch.bfloat16 else lib.vda_forward_f32
-        with torch.cuda.device(dev):
-            st = fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(), gate.data_ptr(),
-                    F, N, H, d_k, d_v, out.data_ptr(), _stream_ptr(dev, stream))
+        st = _call(fn, dev, q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
+                   gate.data_ptr(), F, N, H, d_k, d_v, out.data_ptr(), _stream_ptr(dev, stream))
         _check(st, fn.__name__)
         return out
     if rule not in RULES:
@@ -236,10 +251,9 @@ def forward(q, k, v, beta, gate, out=None, stream=None, alpha=None, text_state=N
                       chunk, radius, offset,
                       gate_tokens.data_ptr() if gate_tokens is not None else None, oh, qh)
     fn = lib.vda_forward_ex if dt == torch.bfloat16 else lib.vda_forward_ex_f32
-    with torch.cuda.device(dev):
-        st = fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
-                gate.data_ptr() if gate is not None else None,
-                F, N, H, d_k, d_v, ctypes.byref(opts), out.data_ptr(), _stream_ptr(dev, stream))
+    st = _call(fn, dev, q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
+               gate.data_ptr() if gate is not None else None, F, N, H, d_k, d_v,
+               ctypes.byref(opts), out.data_ptr(), _stream_ptr(dev, stream))
     _check(st, fn.__name__)
     return out
 
@@ -276,10 +290,9 @@ def text_state(k, v, beta, rule="joint", out=None, stream=None):
         _require(out, "out", torch.float32, dev)
         if tuple(out.shape) != lead + (d_v, d_k):
             raise ValueError(f"out shape {tuple(out.shape)} must be {lead + (d_v, d_k)}")
-    with torch.cuda.device(dev):
-        st = lib.vda_text_state(k.data_ptr(), v.data_ptr(), beta.data_ptr(), L, H, d_k, d_v,
-                                RULES[rule], int(dt == torch.float32), out.data_ptr(),
-                                _stream_ptr(dev, stream))
+    st = _call(lib.vda_text_state, dev, k.data_ptr(), v.data_ptr(), beta.data_ptr(), L, H, d_k,
+               d_v, RULES[rule], int(dt == torch.float32), out.data_ptr(),
+               _stream_ptr(dev, stream))
     _check(st, "vda_text_state")
     return out
 
@@ -305,10 +318,9 @@ def forward_noalloc(q, k, v, beta, gate, out=None, stream=None):
         _require(out, "out", q.dtype, dev)
         if tuple(out.shape) != lead + (F, N, d_v):
             raise ValueError(f"out shape {tuple(out.shape)} must be {lead + (F, N, d_v)}")
-    with torch.cuda.device(dev):
-        st = lib.vda_forward_noalloc(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
-                                     gate.data_ptr(), F, N, H, d_k, d_v, out.data_ptr(),
-                                     _stream_ptr(dev, stream))
+    st = _call(lib.vda_forward_noalloc, dev, q.data_ptr(), k.data_ptr(), v.data_ptr(),
+               beta.data_ptr(), gate.data_ptr(), F, N, H, d_k, d_v, out.data_ptr(),
+               _stream_ptr(dev, stream))
     _check(st, "vda_forward_noalloc")
     return out
 
@@ -369,10 +381,9 @@ def frame_stats(k, v, beta, splits=None, tail_frames=None, A_part=None, B_part=N
         A_part = torch.empty((P, d_k, d_k), dtype=torch.float32, device=dev)
     if B_part is None:
         B_part = torch.empty((P, d_v, d_k), dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        st = lib.vda_frame_stats(k.data_ptr(), v.data_ptr(), beta.data_ptr(), F, N, H, d_k, d_v,
-                                 tail_frames, splits, int(dt == torch.float32), A_part.data_ptr(),
-                                 B_part.data_ptr(), _stream_ptr(dev, stream))
+    st = _call(lib.vda_frame_stats, dev, k.data_ptr(), v.data_ptr(), beta.data_ptr(), F, N, H, d_k,
+               d_v, tail_frames, splits, int(dt == torch.float32), A_part.data_ptr(),
+               B_part.data_ptr(), _stream_ptr(dev, stream))
     _check(st, "vda_frame_stats")
     return A_part, B_part
 
@@ -401,10 +412,9 @@ def frame_inverse(A_part, B_part=None, count=None, tail_frames=0, splits=1, Inv=
                if tiles else
                torch.empty((count, d_k, d_k), dtype=torch.float32, device=A_part.device))
     fn = lib.vda_frame_inverse_tiles if tiles else lib.vda_frame_inverse
-    with torch.cuda.device(A_part.device):
-        st = fn(A_part.data_ptr(), B_part.data_ptr() if B_part is not None else None,
-                int(tail_frames), int(splits), int(count), d_k, d_v, Inv.data_ptr(),
-                _stream_ptr(A_part.device, stream))
+    st = _call(fn, A_part.device, A_part.data_ptr(),
+               B_part.data_ptr() if B_part is not None else None, int(tail_frames), int(splits),
+               int(count), d_k, d_v, Inv.data_ptr(), _stream_ptr(A_part.device, stream))
     _check(st, fn.__name__)
     return Inv
 
@@ -421,10 +431,8 @@ def state_scan(Inv, B, S_fwd=None, S_rev=None, exact_f32=False, stream=None):
         S_fwd = torch.empty((H, F, d_v, d_k), dtype=torch.float32, device=dev)
     if S_rev is None:
         S_rev = torch.empty((H, F, d_v, d_k), dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        st = lib.vda_state_scan(Inv.data_ptr(), B.data_ptr(), F, H, d_k, d_v,
-                                int(bool(exact_f32)), S_fwd.data_ptr(), S_rev.data_ptr(),
-                                _stream_ptr(dev, stream))
+    st = _call(lib.vda_state_scan, dev, Inv.data_ptr(), B.data_ptr(), F, H, d_k, d_v,
+               int(bool(exact_f32)), S_fwd.data_ptr(), S_rev.data_ptr(), _stream_ptr(dev, stream))
     _check(st, "vda_state_scan")
     return S_fwd, S_rev
 
@@ -443,9 +451,8 @@ def state_scan_tiles(Inv_tiles, B, S_fwd=None, S_rev=None, stream=None):
         S_fwd = torch.empty((H, F, d_v, d_k), dtype=torch.float32, device=dev)
     if S_rev is None:
         S_rev = torch.empty((H, F, d_v, d_k), dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        st = lib.vda_state_scan_tiles(Inv_tiles.data_ptr(), B.data_ptr(), F, H, d_k, d_v,
-                                      S_fwd.data_ptr(), S_rev.data_ptr(), _stream_ptr(dev, stream))
+    st = _call(lib.vda_state_scan_tiles, dev, Inv_tiles.data_ptr(), B.data_ptr(), F, H, d_k, d_v,
+               S_fwd.data_ptr(), S_rev.data_ptr(), _stream_ptr(dev, stream))
     _check(st, "vda_state_scan_tiles")
     return S_fwd, S_rev
 
@@ -474,12 +481,11 @@ def state_scan_chunked(Inv_tiles, B, chunk, offset=0, alpha=None, text_state=Non
     if work is None:
         nbytes = chunked_workspace(F, H, d_k, d_v, chunk, offset)
         work = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=dev)
-    with torch.cuda.device(dev):
-        st = lib.vda_state_scan_chunked(
-            Inv_tiles.data_ptr(), B.data_ptr(), alpha.data_ptr() if alpha is not None else None,
-            text_state.data_ptr() if text_state is not None else None, F, H, d_k, d_v, int(chunk),
-            int(offset), work.data_ptr(), S_fwd.data_ptr(), S_rev.data_ptr(),
-            _stream_ptr(dev, stream))
+    st = _call(lib.vda_state_scan_chunked, dev, Inv_tiles.data_ptr(), B.data_ptr(),
+               alpha.data_ptr() if alpha is not None else None,
+               text_state.data_ptr() if text_state is not None else None, F, H, d_k, d_v,
+               int(chunk), int(offset), work.data_ptr(), S_fwd.data_ptr(), S_rev.data_ptr(),
+               _stream_ptr(dev, stream))
     _check(st, "vda_state_scan_chunked")
     return S_fwd, S_rev
 
@@ -520,12 +526,11 @@ def prep(q, k, v, grid, wk_spatial, wk_temporal, wv_spatial, wv_temporal, H, out
                 torch.empty((B * H, F, N, d_v), dtype=torch.bfloat16, device=dev))
     elif (outs[0] is None) != (q is None):
         raise ValueError("q and its output must both be given or both be None")
-    with torch.cuda.device(dev):
-        st = lib.vda_prep(q.data_ptr() if q is not None else None, k.data_ptr(), v.data_ptr(),
-                          wk_spatial.data_ptr(), wk_temporal.data_ptr(), wv_spatial.data_ptr(),
-                          wv_temporal.data_ptr(), B, F, gh, gw, H, d_k, d_v,
-                          outs[0].data_ptr() if outs[0] is not None else None,
-                          outs[1].data_ptr(), outs[2].data_ptr(), _stream_ptr(dev, stream))
+    st = _call(lib.vda_prep, dev, q.data_ptr() if q is not None else None, k.data_ptr(),
+               v.data_ptr(), wk_spatial.data_ptr(), wk_temporal.data_ptr(), wv_spatial.data_ptr(),
+               wv_temporal.data_ptr(), B, F, gh, gw, H, d_k, d_v,
+               outs[0].data_ptr() if outs[0] is not None else None, outs[1].data_ptr(),
+               outs[2].data_ptr(), _stream_ptr(dev, stream))
     _check(st, "vda_prep")
     return outs
 
@@ -538,9 +543,8 @@ def readout(q, S_fwd, S_rev, gate, d_v=None, out=None, stream=None):
     dev = q.device
     if out is None:
         out = torch.empty((H, F, N, d_v), dtype=q.dtype, device=dev)
-    with torch.cuda.device(dev):
-        st = lib.vda_readout(q.data_ptr(), S_fwd.data_ptr(), S_rev.data_ptr(), gate.data_ptr(),
-                             F, N, H, d_k, d_v, int(q.dtype == torch.float32), out.data_ptr(),
-                             _stream_ptr(dev, stream))
+    st = _call(lib.vda_readout, dev, q.data_ptr(), S_fwd.data_ptr(), S_rev.data_ptr(),
+               gate.data_ptr(), F, N, H, d_k, d_v, int(q.dtype == torch.float32), out.data_ptr(),
+               _stream_ptr(dev, stream))
     _check(st, "vda_readout")
     return out
