@@ -488,11 +488,12 @@ hipError_t launch_forward(const ForwardCall& C, char* base, hipStream_t stream) 
   if (e == hipSuccess)
     e = vda::launch_frame_stats(C.is_f32, kx, vx, C.beta, F, N, H, pk, pv, C.plan, A_part, B_part,
                                 stream, /*lower_only=*/!C.frozen);
-  // With bf16 storage the joint rule's inverse is written as split-bf16
-  // operand tiles for the state scan.
+  // The joint rule's inverse is written as the state scan's operand tiles
+  // (split bf16 with bf16 storage, else fp32).
   if (e == hipSuccess && !C.frozen)
-    e = vda::launch_frame_inverse(A_part, B_part, C.plan, (long long)H * F, pk, pv, C.tiled, Inv,
-                                  stream);
+    e = vda::launch_frame_inverse(
+        A_part, B_part, C.plan, (long long)H * F, pk, pv,
+        C.tiled ? vda::InvLayout::kBf16Tiles : vda::InvLayout::kF32Tiles, Inv, stream);
   vda::ScanOptions so;
   so.frozen = C.frozen;
   so.alpha = alpha_x;
@@ -513,7 +514,7 @@ hipError_t launch_forward(const ForwardCall& C, char* base, hipStream_t stream) 
       e = vda::launch_state_scan_tiled(Inv, B_part, F, H, pk, pv, so, S_fwd, S_rev, stream);
     else
       e = vda::launch_state_scan(C.is_f32, C.frozen ? A_part : Inv, B_part, F, H, pk, pv, so,
-                                 S_fwd, S_rev, stream);
+                                 S_fwd, S_rev, stream, /*f32_tiles=*/!C.frozen);
   }
   vda::GatherOptions go;
   go.alpha = alpha_x;
@@ -680,7 +681,8 @@ int text_state_impl(const void* k, const void* v, const float* beta, int L, int 
     e = vda::launch_frame_stats(is_f32 != 0, kx, vx, beta, 1, L, H, pk, pv, plan, A_part, B_part,
                                 stream);
   if (e == hipSuccess && !frozen)
-    e = vda::launch_frame_inverse(A_part, B_part, plan, H, pk, pv, false, A_part, stream);
+    e = vda::launch_frame_inverse(A_part, B_part, plan, H, pk, pv, vda::InvLayout::kRows, A_part,
+                                  stream);
   if (e == hipSuccess)
     e = vda::launch_text_state(B_part, frozen ? nullptr : A_part, H, pk, pv, d_k, d_v,
                                (float)(1.0 / std::sqrt((double)L)), S_T, stream);
@@ -847,7 +849,9 @@ int frame_inverse(const float* A_part, float* B_part, int tail_frames, int split
     if (overlaps(rb, ri) || overlaps(rb, ra)) return VDA_ERR_OVERLAP;
   }
   return hip_status(
-      vda::launch_frame_inverse(A_part, B_part, plan, count, d_k, d_v, tiled, Inv, stream));
+      vda::launch_frame_inverse(A_part, B_part, plan, count, d_k, d_v,
+                                tiled ? vda::InvLayout::kBf16Tiles : vda::InvLayout::kRows, Inv,
+                                stream));
 }
 
 // Checks of the state-scan stage entry points (matrix operand of d_k*d_k*4

@@ -72,6 +72,13 @@ __host__ __device__ constexpr uint32_t operand_tile_offset(int dk, int plane, in
          ((uint32_t)(nb * (dk / 32) + ks) * 64u + (uint32_t)lane) * 16u;
 }
 
+// Layouts in which the inverse writes a d_k x d_k matrix X, of the same size:
+// fp32 by rows; split-bf16 operand tiles (above); or fp32 operand tiles for
+// the fp32 scan's v_mfma_f32_16x16x4_f32, element [16 c + 4 lg + s][16 nb +
+// li] at float ((nb * (d_k / 16) + c) * 64 + li + 16 lg) * 4 + s: one wave's
+// operand of one (nb, c) is 1 KB of contiguous memory.
+enum class InvLayout { kRows, kBf16Tiles, kF32Tiles };
+
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 

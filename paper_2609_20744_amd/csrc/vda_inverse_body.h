@@ -173,7 +173,7 @@ struct WaveColumns {
 };
 
 // One update wave.
-template <int DK, int WV, bool TILED>
+template <int DK, int WV, InvLayout OUT>
 struct UpdateWave {
   static constexpr int NB = DK / 16;
   using Cols = WaveColumns<NB, WV>;
@@ -311,7 +311,12 @@ struct UpdateWave {
         xt = *reinterpret_cast<const floatx4*>(b + li * 20 + 4 * lg);
         __builtin_amdgcn_wave_barrier();
       }
-      if constexpr (TILED) {
+      if constexpr (OUT == InvLayout::kF32Tiles) {
+        // Block (k, n) is lane-ordered piece (nb = n, chunk = k).
+        floatx4* t = reinterpret_cast<floatx4*>(Inv) + lane;
+        t[(C * NB + i) * 64] = x;
+        if (i > C) t[(i * NB + C) * 64] = xt;
+      } else if constexpr (OUT == InvLayout::kBf16Tiles) {
         // Split-bf16 operand tiles (operand_tile_offset): block (k, n) at lane
         // (li, lg) holds X[16k + 4lg + r][16n + li], which is half k % 2 of
         // that lane's 16 bytes of tile (nb = n, ks = k / 2).
@@ -433,9 +438,8 @@ __device__ __forceinline__ void fold_b_partials(float* b0, int splits, size_t lo
 // `lds` is inverse_lds_floats(DK) floats, 16-byte aligned.  The matrix is the
 // sum of `splits` partials at A_part + s * part_stride + base; the result
 // goes to Inv + base (which may alias the first partial: every wave has read
-// its blocks before the first barrier): an fp32 d_k x d_k matrix, or with
-// TILED the split-bf16 operand tiles of the same size in bytes.
-template <int DK, bool TILED>
+// its blocks before the first barrier), d_k * d_k * 4 bytes in layout OUT.
+template <int DK, InvLayout OUT>
 __device__ __forceinline__ void invert_matrix(const float* A_part, int splits, size_t part_stride,
                                               size_t base, float* Inv, float* lds, int tid) {
   constexpr int NB = DK / 16, W = inverse_update_waves(DK);
@@ -449,7 +453,7 @@ __device__ __forceinline__ void invert_matrix(const float* A_part, int splits, s
   const float* a = A_part + base;
   float* out = Inv + base;
   auto update = [&](auto wv) {
-    UpdateWave<DK, decltype(wv)::value, TILED> u;
+    UpdateWave<DK, decltype(wv)::value, OUT> u;
     u.pub = pub;
     u.diag = diag;
     u.lane = lane;

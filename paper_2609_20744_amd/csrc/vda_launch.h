@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "vda_common.h"
+
 namespace vda {
 
 // Split plan of the statistics step: the last `tail` of the `count` frames
@@ -33,12 +35,11 @@ hipError_t launch_frame_stats(bool is_f32, const void* k, const void* v, const f
                               float* A_part, float* B_part, hipStream_t stream,
                               bool lower_only = false);
 
-// Step a2, Eq. 5: Inv = (I + sum of A partials)^{-1} (fp32 matrices, or
-// split-bf16 operand tiles when `tiled`); also folds the B partials of every
+// Step a2, Eq. 5: Inv = (I + sum of A partials)^{-1}, in layout `out`; also folds the B partials of every
 // split frame into its first partial.  It reads only A_t's blocks on and
 // below the diagonal.
 hipError_t launch_frame_inverse(const float* A_part, float* B_part, SplitPlan plan,
-                                long long count, int d_k, int d_v, bool tiled, float* Inv,
+                                long long count, int d_k, int d_v, InvLayout out, float* Inv,
                                 hipStream_t stream);
 
 // Options of the scans beyond the core (defaults: the core scan).
@@ -51,10 +52,11 @@ struct ScanOptions {
 
 // Steps a3/a4, Eq. A.1: forward and reverse state scans (exact fp32 products,
 // or split-bf16 products with fp32 accumulation).  Mat is Inv_t (joint rule)
-// or A_t (frozen rule), symmetric.
+// or A_t (frozen rule), symmetric; f32_tiles (exact_f32 and joint rule only):
+// Inv_t as fp32 operand tiles (InvLayout::kF32Tiles), not by rows.
 hipError_t launch_state_scan(bool exact_f32, const float* Mat, const float* Bm, int F, int H,
                              int d_k, int d_v, const ScanOptions& o, float* S_fwd, float* S_rev,
-                             hipStream_t stream);
+                             hipStream_t stream, bool f32_tiles = false);
 
 // The frozen rule (Eq. 3c with the 1/sqrt(U) scaling) on the tiled scan:
 // launch_frozen_tiles overwrites each A_t [H][F][d_k][d_k] in place with the

@@ -7,19 +7,17 @@
 // The rows of the d_v x d_k state evolve independently (each is a row vector
 // times Inv_t), so a chain (head, direction) is split into 16-row blocks,
 // one workgroup each, and the frame loop runs inside the workgroup with the
-// 16 x d_k block resident in LDS (double-buffered, fp32).  Per frame the four
-// wavefronts multiply the block by Inv_t, each producing d_k/64 16-column
-// slices.  Inv_t is symmetric ((I + A_t)^{-1} of a symmetric A_t), so the
-// k-th column slice a lane needs is read as a contiguous piece of row j of
-// Inv_t with 16-byte loads.  Inv_t and B_t of the next two frames are in
-// flight in a register ring, so memory latency stays off the serial path,
-// which holds only the matrix product and two barriers.  Workgroups of one
-// chain are placed on one XCD so they share Inv_t in its L2.
+// 16 x d_k block of the state on chip, in fp32.  Per frame the wavefronts
+// multiply the block by Inv_t, each producing some 16-column slices.  The
+// matrices and B_t of the next two frames are in flight in a register ring,
+// so memory latency stays off the serial path, which holds only the matrix
+// product and its barriers.  Workgroups of one chain are placed on one XCD so
+// they share Inv_t in its L2.
 //
-// Products: with fp32 storage (scan_kernel), v_mfma_f32_16x16x4_f32 (exact
-// fp32 products).  With bf16 storage (scan_bf16_kernel, which also stages
-// Inv_t through LDS, see there), each fp32 operand x is split into bf16
-// hi = bf16(x) and lo = bf16(x - hi), and the product is hi*hi + hi*lo +
+// Products: with fp32 storage (scan_f32_kernel), v_mfma_f32_16x16x4_f32
+// (exact fp32 products).  With bf16 storage (scan_bf16_kernel, which also
+// stages Inv_t through LDS, see there), each fp32 operand x is split into
+// bf16 hi = bf16(x) and lo = bf16(x - hi), and the product is hi*hi + hi*lo +
 // lo*hi on v_mfma_f32_16x16x32_bf16 with fp32 accumulation (about 16
 // mantissa bits per operand, relative error ~1e-5), several times the fp32
 // matrix rate.
@@ -39,27 +37,36 @@ __device__ __forceinline__ void split_bf16x8(const float (&x)[8], bf16x8& hi, bf
 }
 
 // The exact fp32 scan (fp32 storage path); DECAY and FROZEN as described at
-// scan_bf16_kernel below.
-template <int DK, bool FROZEN, bool DECAY>
-__global__ __launch_bounds__(kThreads)
+// scan_bf16_kernel below.  As in the tiled scan of the bf16 path the product
+// is formed transposed, Inv_t x^T: its result leaves a lane four
+// consecutive columns of one state row, which are its B-operand of the next
+// product (v_mfma_f32_16x16x4_f32, lane group lg of k chunk c supplying k =
+// 16 c + 4 lg + s in product s).  So each of NB / NBW waves keeps its NBW
+// 16-column blocks of the 16 rows in registers and hands them to the others
+// through LDS, double buffered, one barrier per step; B_t and the entering
+// states pass through the wave's own LDS, so that memory sees whole runs of
+// a row.  Inv_t comes as fp32 operand tiles (TILES, from the inverse in
+// vda_forward's fp32 path) or by rows (the stage entry point; A_t of the
+// frozen rule), of which it is symmetric; two steps ahead, each chunk
+// refilled as its products are issued.  By rows a load takes 16 bytes of a
+// different row per lane, and those loads bound the step: 52 us for
+// 4 heads x 21 frames of 128 x 128 (51 before the state stayed in registers),
+// and 37 from tiles, of which the products' issue is 19.
+template <int DK, bool FROZEN, bool DECAY, bool TILES>
+__global__ __launch_bounds__(DK == 32 ? 128 : 256) __attribute__((amdgpu_waves_per_eu(2)))
 void scan_f32_kernel(const float* __restrict__ Mat, const float* __restrict__ Bm,
                      const float* __restrict__ alpha, const float* __restrict__ text_state,
                      int F, int DV, unsigned nwg, float inv_u, float inv_sqrt_u,
                      float* __restrict__ S_fwd, float* __restrict__ S_rev) {
-  constexpr int XLD = DK + 4;        // LDS row stride (floats)
-  constexpr int NB = DK / 16;        // 16-column output slices
-  constexpr int NBW = (NB + 3) / 4;  // slices per wave
-  // k values per lane and slice: value s is k = 16 (s / 4) + 4 lg + s % 4, so
-  // the four lane groups of a row read one 64-byte run of it per load.
-  constexpr int KL = DK / 4;
-  constexpr int E = DK / 16;         // state elements per thread in the row-wise phase
-  static_assert(E % 2 == 0, "float2 granularity");
-  // Row-wise accesses in 16-byte pieces where the row slice allows: fewer
-  // memory operations keep the prefetch ring within what the hardware's
-  // outstanding-load counter can track precisely.
-  constexpr int VW = E % 4 == 0 ? 4 : 2;
-  __shared__ __align__(16) float xs[2][16 * XLD];
-  __shared__ __align__(16) float alds[DECAY ? DK : 4];  // alpha of the coming step
+  constexpr int NB = DK / 16;                 // 16-column blocks, and k chunks
+  constexpr int NBW = DK == 128 ? 2 : 1;      // blocks per wave
+  constexpr int W = NB / NBW;                 // waves
+  constexpr int kRow = 16 * NBW + 4;          // floats per row of a wave's blocks in LDS
+  constexpr int LPR = 4 * NBW;                // lanes per row in memory order
+  constexpr int RPI = 64 / LPR;               // rows per access in memory order
+  static_assert(16 / RPI == NBW, "as many accesses in either order");
+  __shared__ floatx4 xop[2][NB][64];          // the state's operand: [step parity][chunk][lane]
+  __shared__ __align__(16) float xb[W][16 * kRow], xs[W][16 * kRow];
 
   const int nrb = DV / 16;
   const unsigned L = xcd_grouped_id(blockIdx.x, nwg);
@@ -74,174 +81,149 @@ void scan_f32_kernel(const float* __restrict__ Mat, const float* __restrict__ Bm
   const int li = lane & 15;
   const int lg = lane >> 4;
 
-  // Row-wise phase role: row pr of the block, columns pc .. pc+E-1.
-  const int pr = tid >> 4;
-  const int pc = (tid & 15) * E;
-
   const size_t mat_b = (size_t)DV * DK;  // one B / state matrix
-  for (int i = tid; i < 16 * XLD; i += kThreads) {
-    const int r = i / XLD, c = i % XLD;
-    xs[0][i] = text_state != nullptr && c < DK
-                   ? 0.5f * text_state[(size_t)hb * mat_b + (size_t)(rb * 16 + r) * DK + c]
-                   : 0.f;
-  }
+  // This lane's state: row rb * 16 + li, columns col + 16 j + r (j < NBW, r < 4).
+  const int col = 16 * NBW * wave + 4 * lg;
+  // In memory order: row mrow + RPI j, columns mcol .. mcol + 3 of the wave's.
+  const int mrow = lane / LPR, mcol = (lane % LPR) * 4;
+  const uint32_t mem_off = (uint32_t)((rb * 16 + mrow) * DK + 16 * NBW * wave + mcol) * 4u;
+  float* const bm = &xb[wave][mrow * kRow + mcol];
+  const float* const bx = &xb[wave][li * kRow + 4 * lg];
+  float* const sx = &xs[wave][li * kRow + 4 * lg];
+  const float* const sm = &xs[wave][mrow * kRow + mcol];
+  floatx4 x[NBW];
+#pragma unroll
+  for (int j = 0; j < NBW; ++j)
+    x[j] = text_state != nullptr
+               ? 0.5f * *reinterpret_cast<const floatx4*>(text_state + (size_t)hb * mat_b +
+                                                          (size_t)(rb * 16 + li) * DK + col + 16 * j)
+               : floatx4{0.f, 0.f, 0.f, 0.f};
 
   float* Sout = dir == 0 ? S_fwd : S_rev;
-  const size_t row_off = (size_t)(rb * 16 + pr) * DK + pc;
   const __amdgpu_buffer_rsrc_t srsrc =
       make_rsrc(Sout + (size_t)hb * F * mat_b, (uint32_t)(F * mat_b * sizeof(float)));
   const __amdgpu_buffer_rsrc_t brsrc =
       make_rsrc(Bm + (size_t)hb * F * mat_b, (uint32_t)(F * mat_b * sizeof(float)));
   const __amdgpu_buffer_rsrc_t arsrc =
       make_rsrc(DECAY ? alpha + (size_t)hb * F * DK : Bm, DECAY ? (uint32_t)(F * DK * 4) : 0u);
+  const __amdgpu_buffer_rsrc_t mrsrc =
+      make_rsrc(Mat + (size_t)hb * F * (DK * DK), (uint32_t)F * (uint32_t)(DK * DK * 4));
 
   auto frame_of = [&](int step) { return dir == 0 ? step : F - 1 - step; };
 
-  // Operands of the next two frames are in flight in a register ring: slot
-  // d holds frame step0 + d, refilled with frame step0 + d + 2 once
-  // consumed.  A deeper ring no longer fits in the vector registers.
-  constexpr int kPrefetch = 2;
-  float ops[kPrefetch][NBW][KL];
-  float bs[kPrefetch][E];
-  u32x4 al[kPrefetch];  // alpha, columns 4 tid .. 4 tid + 3 (threads tid < DK / 4)
-  // Values 4 c .. 4 c + 3 of every slice's operand of step `step`.
-  auto load_mat = [&](int step, int c, float (&op)[NBW][KL]) {
-    const float* mat = Mat + ((size_t)hb * F + frame_of(step)) * (DK * DK);
-#pragma unroll
-    for (int m = 0; m < NBW; ++m) {
-      const int nb = wave + 4 * m;
-      if (NB >= 4 || nb < NB) {  // compile-time true unless d_k = 32
-        // Mat[k][nb*16 + li] == Mat[nb*16 + li][k] (symmetric)
-        const float4 v = *reinterpret_cast<const float4*>(mat + (size_t)(nb * 16 + li) * DK +
-                                                          16 * c + 4 * lg);
-        op[m][4 * c] = v.x;
-        op[m][4 * c + 1] = v.y;
-        op[m][4 * c + 2] = v.z;
-        op[m][4 * c + 3] = v.w;
-      }
-    }
+  // Two-slot register ring, as separately named arrays: step s uses slot
+  // s % 2, whose registers take step s + 2 (past the end: a clamped, unused
+  // step, so no branch hides the loads from the wait-count bookkeeping).
+  struct Slot {
+    floatx4 m[NBW][NB];  // rows 16 (NBW wave + j) + li of the matrix, by chunk
+    floatx4 b[NBW];      // B_t (frozen: of the frame before), memory order
+    floatx4 al[NBW];     // alpha_t
   };
-  auto load_add = [&](int step, float (&bb)[E], u32x4& av) {
-    const int frame = frame_of(step);
-    const int bframe = FROZEN ? frame_of(step - 1) : frame;
-    const bool bin = (unsigned)bframe < (unsigned)F;
+  Slot s0, s1;
+  auto load_add = [&](int step, Slot& s) {
+    const int bframe = FROZEN ? frame_of(step - 1) : frame_of(step);
+    const uint32_t off = (uint32_t)bframe * (uint32_t)(mat_b * 4u) + mem_off;
 #pragma unroll
-    for (int e = 0; e < E; e += VW) {
-      const uint32_t off =
-          bin ? (uint32_t)(((size_t)bframe * mat_b + row_off + e) * 4u) : kOutOfRange;
-      if constexpr (VW == 4) {
-        const u32x4 x =
-            __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, (int)off, 0, 0));
-#pragma unroll
-        for (int v = 0; v < 4; ++v) bb[e + v] = __uint_as_float(x[v]);
-      } else {
-        const u32x2 x =
-            __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(brsrc, (int)off, 0, 0));
-        bb[e] = __uint_as_float(x[0]);
-        bb[e + 1] = __uint_as_float(x[1]);
-      }
-    }
+    for (int j = 0; j < NBW; ++j)
+      s.b[j] = __builtin_bit_cast(
+          floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                       brsrc, (int)((unsigned)bframe < (unsigned)F ? off + (uint32_t)(RPI * DK * 4 * j)
+                                                                   : kOutOfRange),
+                       0, 0));
     if constexpr (DECAY) {
-      const uint32_t off = tid < DK / 4 ? (uint32_t)(frame * DK + 4 * tid) * 4u : kOutOfRange;
-      av = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(arsrc, (int)off, 0, 0));
+#pragma unroll
+      for (int j = 0; j < NBW; ++j)
+        s.al[j] = __builtin_bit_cast(
+            floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                         arsrc, (int)((uint32_t)(frame_of(step) * DK + col + 16 * j) * 4u), 0, 0));
     }
   };
+  const uint32_t moff = TILES ? (uint32_t)(NBW * wave * NB * 1024 + lane * 16)
+                              : (uint32_t)((16 * NBW * wave + li) * DK + 4 * lg) * 4u;
+  auto load_chunk = [&](int step, Slot& s, int c) {
+    const uint32_t base = (uint32_t)frame_of(step) * (uint32_t)(DK * DK * 4);
+#pragma unroll
+    for (int j = 0; j < NBW; ++j)
+      s.m[j][c] = __builtin_bit_cast(
+          floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                       mrsrc, (int)(moff + (TILES ? (uint32_t)((j * NB + c) * 1024)
+                                                 : (uint32_t)((16 * j * DK + 16 * c) * 4))),
+                       (int)base, 0));
+  };
 
+  // B of the coming step in the products' order (a wave's LDS operations run
+  // in order).
+  floatx4 bn[NBW];
+  auto turn_b = [&](const Slot& s) {
 #pragma unroll
-  for (int d = 0; d < kPrefetch; ++d) {
-    load_add(min(d, F - 1), bs[d], al[d]);
+    for (int j = 0; j < NBW; ++j) *reinterpret_cast<floatx4*>(bm + RPI * kRow * j) = s.b[j];
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int c = 0; c < KL / 4; ++c) load_mat(min(d, F - 1), c, ops[d]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  if constexpr (DECAY) {
-    if (tid < DK / 4) reinterpret_cast<u32x4*>(alds)[tid] = al[0];
-  }
+    for (int j = 0; j < NBW; ++j) bn[j] = *reinterpret_cast<const floatx4*>(bx + 16 * j);
+    __builtin_amdgcn_wave_barrier();
+  };
 
-  int cur = 0;
-  for (int step0 = 0; step0 < F; step0 += kPrefetch) {
+  // Step `step` on slot s; o is the other slot, the coming step's.
+  auto step_body = [&](int step, int par, Slot& s, const Slot& o) {
 #pragma unroll
-    for (int d = 0; d < kPrefetch; ++d) {
-      const int step = step0 + d;
-      const int frame = dir == 0 ? step : F - 1 - step;
-      lds_barrier();  // xs[cur] holds the entering state
-      {
-        float* x = &xs[cur][pr * XLD + pc];
-        const uint32_t off = (uint32_t)((size_t)(unsigned)frame * mat_b + row_off) * 4u;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          if constexpr (FROZEN) x[e] += bs[d][e] * inv_sqrt_u;  // previous frame's write
-        }
-#pragma unroll
-        for (int e = 0; e < E; e += VW) {
-          if constexpr (VW == 4) {
-            const float4 v = *reinterpret_cast<float4*>(x + e);
-            store_b128(srsrc, off + e * 4u,
-                       u32x4{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
-                             __float_as_uint(v.w)});
-          } else {
-            const float2 v = *reinterpret_cast<float2*>(x + e);
-            store_b64(srsrc, off + e * 4u, make_uint2(__float_as_uint(v.x), __float_as_uint(v.y)));
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          float v = x[e];
-          if constexpr (DECAY) v *= alds[pc + e];
-          if constexpr (!FROZEN) v += bs[d][e];
-          x[e] = v;
-        }
+    for (int j = 0; j < NBW; ++j) {
+      floatx4 u;
+      if constexpr (FROZEN) {
+        x[j] += bn[j] * inv_sqrt_u;  // the previous frame's write
+        u = DECAY ? x[j] * s.al[j] : x[j];
+      } else {
+        u = DECAY ? x[j] * s.al[j] + bn[j] : x[j] + bn[j];
       }
-      lds_barrier();
-      if constexpr (DECAY) {  // alpha of the next step (this step's reads are done)
-        if (tid < DK / 4) reinterpret_cast<u32x4*>(alds)[tid] = al[(d + 1) % kPrefetch];
-      }
-      // Always refill (past the end: a clamped, unused frame) so no branch
-      // hides the loads from the wait-count bookkeeping.
-      const int refill = min(step + kPrefetch, F - 1);
-      load_add(refill, bs[d], al[d]);
-      if (NB >= 4 || wave < NB) {
-        // A-operand: row li of the block at the same k.
-        float a[KL];
-        const float* xr = &xs[cur][li * XLD + 4 * lg];
-#pragma unroll
-        for (int s = 0; s < KL; s += 4) {
-          const float4 v = *reinterpret_cast<const float4*>(xr + 4 * s);
-          a[s] = v.x;
-          a[s + 1] = v.y;
-          a[s + 2] = v.z;
-          a[s + 3] = v.w;
-        }
-        // The slices advance together, even and odd k in separate
-        // accumulators (four independent chains at d_k = 128); each chunk's
-        // operand registers are refilled as soon as its products are issued.
-        // (Slice by slice on one chain, refilled after the last product, with
-        // 16-byte reads 128 bytes apart: 2.9 us a step at d_k = d_v = 128;
-        // 2.4 now, of which the products' issue is 0.9.)
-        floatx4 acc[NBW][2];
-#pragma unroll
-        for (int m = 0; m < NBW; ++m) acc[m][0] = acc[m][1] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < KL / 4; ++c) {
-#pragma unroll
-          for (int s = 4 * c; s < 4 * c + 4; ++s)
-#pragma unroll
-            for (int m = 0; m < NBW; ++m) {
-              float b = ops[d][m][s];
-              if constexpr (FROZEN)  // I - A / U
-                b = (16 * c + 4 * lg + s % 4 == (wave + 4 * m) * 16 + li ? 1.0f : 0.0f) - b * inv_u;
-              acc[m][s & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b, acc[m][s & 1], 0, 0, 0);
-            }
-          load_mat(refill, c, ops[d]);
-        }
-#pragma unroll
-        for (int m = 0; m < NBW; ++m)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            xs[cur ^ 1][(lg * 4 + i) * XLD + (wave + 4 * m) * 16 + li] = acc[m][0][i] + acc[m][1][i];
-      }
-      cur ^= 1;
+      xop[par][NBW * wave + j][lane] = u;
+      *reinterpret_cast<floatx4*>(sx + 16 * j) = x[j];  // the entering state, on its way to memory
     }
+    lds_barrier();  // the state's operand is complete
+    floatx4 y[NBW];
+#pragma unroll
+    for (int j = 0; j < NBW; ++j) y[j] = *reinterpret_cast<const floatx4*>(sm + RPI * kRow * j);
+    const int refill = min(step + 2, F - 1);
+    load_add(refill, s);
+    turn_b(o);
+    const uint32_t soff = (uint32_t)frame_of(step) * (uint32_t)(mat_b * 4u) + mem_off;
+#pragma unroll
+    for (int j = 0; j < NBW; ++j)
+      store_b128(srsrc, step < F ? soff + (uint32_t)(RPI * DK * 4 * j) : kOutOfRange,
+                 __builtin_bit_cast(u32x4, y[j]));
+    // Even and odd products in separate accumulators.
+    floatx4 acc[NBW][2];
+#pragma unroll
+    for (int j = 0; j < NBW; ++j) acc[j][0] = acc[j][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+      const floatx4 xv = xop[par][c][lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < NBW; ++j) {
+          float m = s.m[j][c][e];
+          if constexpr (FROZEN)  // I - A / U
+            m = (16 * c + 4 * lg + e == 16 * (NBW * wave + j) + li ? 1.0f : 0.0f) - m * inv_u;
+          acc[j][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(m, xv[e], acc[j][e & 1], 0, 0, 0);
+        }
+      load_chunk(refill, s, c);
+    }
+#pragma unroll
+    for (int j = 0; j < NBW; ++j) x[j] = acc[j][0] + acc[j][1];
+  };
+
+  auto fill = [&](int step, Slot& s) {
+    load_add(step, s);
+#pragma unroll
+    for (int c = 0; c < NB; ++c) load_chunk(step, s, c);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  fill(0, s0);
+  fill(min(1, F - 1), s1);
+  turn_b(s0);
+  // A padded step (step >= F) reads a clamped matrix and stores nothing.
+  for (int step = 0; step < F; step += 2) {
+    step_body(step, 0, s0, s1);
+    step_body(step + 1, 1, s1, s0);
   }
 }
 
@@ -345,7 +327,7 @@ __device__ __forceinline__ void scan_mfma_phase(const uint16_t* __restrict__ xhi
 
 // The split-bf16 scan (bf16 storage path).  The recurrence, the work split
 // (one 16-row block of one chain per workgroup) and the products are those
-// of scan_kernel; the difference is how Inv_t reaches the matrix cores.
+// of scan_f32_kernel; the difference is how Inv_t reaches the matrix cores.
 // Per frame the workgroup copies only the blocks of Inv_t on and above the
 // diagonal (36 of 64 at d_k = 128; the others are their transposes, as
 // Inv_t is symmetric) with consecutive lanes on consecutive 16-byte chunks
@@ -609,13 +591,24 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
 
 template <int DK, bool FROZEN, bool DECAY>
 hipError_t launch_scan_v(bool exact_f32, const float* Mat, const float* Bm, int F, int H, int d_v,
-                         const ScanOptions& o, float* S_fwd, float* S_rev, hipStream_t stream) {
+                         const ScanOptions& o, bool f32_tiles, float* S_fwd, float* S_rev,
+                         hipStream_t stream) {
   const unsigned nwg = (unsigned)H * 2u * (unsigned)(d_v / 16);
   const float inv_u = FROZEN ? 1.0f / (float)o.tokens : 0.0f;
   const float inv_sqrt_u = FROZEN ? 1.0f / sqrtf((float)o.tokens) : 0.0f;
   if (exact_f32) {
-    hipLaunchKernelGGL((scan_f32_kernel<DK, FROZEN, DECAY>), dim3(nwg), dim3(kThreads), 0, stream,
-                       Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd, S_rev);
+    const dim3 block(DK == 32 ? 128 : 256);
+    if (f32_tiles) {
+      if constexpr (FROZEN) return hipErrorInvalidValue;
+      else
+        hipLaunchKernelGGL((scan_f32_kernel<DK, false, DECAY, true>), dim3(nwg), block, 0, stream,
+                           Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd,
+                           S_rev);
+    } else {
+      hipLaunchKernelGGL((scan_f32_kernel<DK, FROZEN, DECAY, false>), dim3(nwg), block, 0, stream,
+                         Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd,
+                         S_rev);
+    }
   } else {
     // With bf16 storage the frozen rule runs on the tiled scan (map form).
     if constexpr (FROZEN) return hipErrorInvalidValue;
@@ -628,24 +621,29 @@ hipError_t launch_scan_v(bool exact_f32, const float* Mat, const float* Bm, int 
 
 template <int DK>
 hipError_t launch_scan_t(bool exact_f32, const float* Mat, const float* Bm, int F, int H, int d_v,
-                         const ScanOptions& o, float* S_fwd, float* S_rev, hipStream_t stream) {
+                         const ScanOptions& o, bool f32_tiles, float* S_fwd, float* S_rev,
+                         hipStream_t stream) {
   const bool decay = o.alpha != nullptr;
   if (o.frozen)
-    return decay ? launch_scan_v<DK, true, true>(exact_f32, Mat, Bm, F, H, d_v, o, S_fwd, S_rev, stream)
-                 : launch_scan_v<DK, true, false>(exact_f32, Mat, Bm, F, H, d_v, o, S_fwd, S_rev, stream);
-  return decay ? launch_scan_v<DK, false, true>(exact_f32, Mat, Bm, F, H, d_v, o, S_fwd, S_rev, stream)
-               : launch_scan_v<DK, false, false>(exact_f32, Mat, Bm, F, H, d_v, o, S_fwd, S_rev, stream);
+    return decay ? launch_scan_v<DK, true, true>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
+                                            stream)
+                 : launch_scan_v<DK, true, false>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
+                                            stream);
+  return decay ? launch_scan_v<DK, false, true>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
+                                            stream)
+               : launch_scan_v<DK, false, false>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
+                                            stream);
 }
 
 }  // namespace
 
 hipError_t launch_state_scan(bool exact_f32, const float* Mat, const float* Bm, int F, int H,
                              int d_k, int d_v, const ScanOptions& o, float* S_fwd, float* S_rev,
-                             hipStream_t stream) {
+                             hipStream_t stream, bool f32_tiles) {
   switch (d_k) {
-    case 32: return launch_scan_t<32>(exact_f32, Mat, Bm, F, H, d_v, o, S_fwd, S_rev, stream);
-    case 64: return launch_scan_t<64>(exact_f32, Mat, Bm, F, H, d_v, o, S_fwd, S_rev, stream);
-    case 128: return launch_scan_t<128>(exact_f32, Mat, Bm, F, H, d_v, o, S_fwd, S_rev, stream);
+    case 32: return launch_scan_t<32>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev, stream);
+    case 64: return launch_scan_t<64>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev, stream);
+    case 128: return launch_scan_t<128>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -62,3 +62,22 @@ def test_readout(V, H, N, dk, dv):
     # The norm's own sum of d_v squares (relative error U * d_v / 2), root, quotient and product.
     bound = g / rms * (do + np.abs(o) / rms * do.max(-1, keepdims=True)) + U * (dv / 2 + 8) * np.abs(ref)
     assert np.all(np.abs(y - ref) <= bound)
+
+
+# The scan from fp32 operand tiles (vda_forward) does the sums of the scan from rows (the stage) in the same order, so
+# the two passes agree bit for bit: one step and no step in flight, every depth of the ring, and more heads than XCDs.
+@pytest.mark.parametrize("H,F", [(1, 1), (2, 2), (1, 3), (3, 5), (9, 8)])
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 32), (32, 128), (128, 64)])
+def test_scan_tiles(V, H, F, dk, dv):
+    import torch
+    N = 33
+    rng = np.random.default_rng(H + F + dk + dv)
+    q, k = (to_device((x / np.linalg.norm(x, axis=-1, keepdims=True)).astype(np.float32), "f32")
+            for x in (rng.standard_normal((H, F, N, dk)) for _ in range(2)))
+    v = to_device(rng.standard_normal((H, F, N, dv)).astype(np.float32), "f32")
+    beta, gate = (to_device(rng.random(s).astype(np.float32), "f32") for s in ((H, F, N), (H,)))
+    tail, splits = V.default_split_plan(F, N, H, dk, dv, is_f32=True)
+    A, B = V.frame_stats(k, v, beta, splits=splits, tail_frames=tail)
+    inv = V.frame_inverse(A, B, count=H * F, tail_frames=tail, splits=splits)
+    sf, sr = V.state_scan(inv.view(H, F, dk, dk), B[:H * F].view(H, F, dv, dk), exact_f32=True)
+    assert torch.equal(V.forward(q, k, v, beta, gate), V.readout(q, sf, sr, gate, d_v=dv))
