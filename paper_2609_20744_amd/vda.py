@@ -127,6 +127,8 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream_ptr(device, stream=None) -> int:
+    if device.type != "cuda":
+        torch.cuda.device(device)  # raises: not a cuda device
     if stream is not None:
         return int(stream.cuda_stream)
     if _raw_stream is not None and device.index is not None:
