@@ -84,11 +84,12 @@ def instance_of(w):
     """The template instance of each stage's kernel that one pass of the
     workload runs (bf16 storage); the summary reads its counters, not those
     of other instances of the same kernel (the chunk-wise and frozen-rule
-    scans share the scan kernel's name).  The prep convolution keeps its bare
-    name: its K and V launches are two instances, averaged."""
+    scans share the scan kernel's name).  The statistics keep their bare name
+    (a pass runs one instance, whose load policy goes by the size), and so
+    does the prep convolution: its K and V launches are two instances,
+    averaged."""
     dk, dv = w.d_k, w.d_v
-    return {"frame_stats": f"stats_bf16_kernel<{dk},{dv}>",
-            "frame_inverse": f"inverse_kernel<{dk},true>",
+    return {"frame_inverse": f"inverse_kernel<{dk},1>",  # (1: written as bf16 operand tiles)
             "state_scan": f"scan_tiled_kernel<{dk},false,false>",
             "readout": f"readout_bf16_kernel<{dk},{dv},false,false>",
             "prep_qnorm": f"prep_qnorm_kernel<{dk}>"}
