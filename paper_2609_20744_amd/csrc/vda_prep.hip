@@ -24,12 +24,11 @@
 // wave for K) and stored.  Every input is read from memory once per tile
 // that needs it (tiles sharing a halo run on one XCD, so the re-reads hit
 // its L2) and every output is written once.  The work is bound by the fp32
-// FMAs (25 + 5 per output channel): 480 of ~700 vector instructions per wave
+// FMAs (25 + 5 per output channel): 480 of ~720 vector instructions per wave
 // and frame, and two quarter-rate ones per output.  At 16 heads x 36 frames x
 // 48 x 80 tokens, d = 128, K takes 430 us and V 394 in a trace; 461 and 425
-// with ~760 instructions (log2(e) multiplied in SiLU instead of once into the
-// taps, sums cleared instead of set by the first tap, addresses of whole
-// clips).  The filter on 4 x 4 x 4 matrix products with the taps in three
+// with ~760 instructions (sums cleared instead of set by the first tap,
+// addresses of whole clips).  The filter on 4 x 4 x 4 matrix products with the taps in three
 // bf16 parts issues half the instructions and takes 491 and 413 us: the small
 // products and the vector instructions share the issue port.
 //
@@ -49,15 +48,13 @@ constexpr int kPTY = 8, kPTX = 8;                    // output tile (rows = wave
 constexpr int kPHY = kPTY + 4, kPHX = kPTX + 4;      // with the 2-token halo
 static_assert(kPTX == 8, "the L2 reduction sums eight tokens per wave row");
 
-// The temporal taps carry a factor log2(e), so a convolution's value arrives
-// as z = x log2(e), ready for the hardware's base-2 exponential.
-constexpr float kLog2e = 1.44269504088896340736f;
-
-// SiLU x / (1 + exp(-x)) of x = z / log2(e), with the hardware reciprocal (1
-// ulp): z / (log2(e) + log2(e) 2^-z).  For z -> -inf the exponential
-// overflows to inf and the result is -0, the limit.
-__device__ __forceinline__ float silu_log2e(float z) {
-  return z * __builtin_amdgcn_rcpf(fmaf(__builtin_amdgcn_exp2f(-z), kLog2e, kLog2e));
+// SiLU with the hardware reciprocal (1 ulp).  For x -> -inf, exp(-x)
+// overflows to inf and the result is -0, the limit, for every finite x: so
+// log2(e) is multiplied in here and not once into the temporal taps, which
+// would let the running sums of |x| > FLT_MAX / log2(e) overflow (an output
+// of NaN where x < 0, of inf where x > 0).
+__device__ __forceinline__ float silu(float x) {
+  return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x));
 }
 
 #define VDA_DPP(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
@@ -146,7 +143,7 @@ void prep_conv_kernel(PrepConvArgs a) {
 #pragma unroll
     for (int i = 0; i < 25; ++i) wsp[c][i] = a.ws[(size_t)ch * 25 + i];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) wtp[c][i] = a.wt[(size_t)ch * 5 + i] * kLog2e;
+    for (int i = 0; i < 5; ++i) wtp[c][i] = a.wt[(size_t)ch * 5 + i];
   }
 
   // One input frame's haloed tile: chunk q (16 bytes) of the tile is piece
@@ -257,7 +254,7 @@ void prep_conv_kernel(PrepConvArgs a) {
         scale[x] = 0.f;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-          y[x][c] = silu_log2e(ring[OS][x][c]);
+          y[x][c] = silu(ring[OS][x][c]);
           scale[x] = fmaf(y[x][c], y[x][c], scale[x]);
         }
       }

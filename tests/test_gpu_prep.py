@@ -179,3 +179,26 @@ def test_raw_query_pipeline(V, d):
         err = rel_max_err(from_device(y), ref)
         _log(f"  {name}: rel err {err:.2e}")
         assert err <= 2e-2, (name, err)
+
+
+# Taps of one at the centre, so a token's convolution is its input: the ends of bf16's range, values whose exponential
+# is near its own range, and ordinary ones.  SiLU's limit is -0 for large negative values and x for large positive ones,
+# and a key of more than 1.8e19 has a sum of squares that is inf in fp32, of which it is normalised to 0.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("x", [-3.3895313892515355e38, -3.0e38, -2.4e38, -1.0e38, -88.5, -87.0, -1.0, 1.0, 89.0, 2.4e38,
+                               3.0e38, 3.3895313892515355e38])
+def test_prep_range(V, x, d):
+    import torch
+    B, F, grid, H = 1, 3, (3, 5), 1
+    X = torch.full((B, F, grid[0] * grid[1], H * d), x, dtype=torch.bfloat16)
+    xv = float(X[0, 0, 0, 0])
+    ws, wt = torch.zeros(H * d, 25), torch.zeros(H * d, 5)
+    ws[:, 12] = 1.0
+    wt[:, 2] = 1.0
+    ws, wt = ws.cuda(), wt.cuda()
+    _, k, v = V.prep(None, X.cuda(), X.cuda(), grid, ws, wt, ws, wt, H)
+    y = xv / (1.0 + np.exp(-xv)) if xv > -700.0 else -0.0
+    # (The hardware reciprocal is 0 below 2^-126, and |x| < 2^7 where that leaves a value.)
+    assert np.all(np.abs(from_device(v) - y) <= TOL_PREP * abs(y) + 2.0 ** -119), x
+    norm = 0.0 if abs(y) > 1e19 else y / np.sqrt(d * y * y + 1e-6)
+    assert np.all(np.abs(from_device(k) - norm) <= TOL_PREP * abs(norm) + 2.0 ** -100), x
