@@ -365,9 +365,9 @@ int vda_workspace_bytes(int device, size_t* bytes);
  * vda_default_split_plan -- the plan vda_forward uses on the current device
  * for these sizes and storage type (is_f32 != 0: fp32).  Whole frames occupy
  * the device in rounds; when the last round is partial its frames are split
- * (at most 4 ranges of at least 256 tokens; fp32 storage: 8 of at least
- * 128).  Writes *tail_frames and
- * *splits.
+ * (at most N / 256 ranges and 4; fp32 storage: N / 128 and 8).  Ranges are
+ * equal but for the last, which has what the others, a multiple of 64 tokens
+ * each, leave of N: at least one token.  Writes *tail_frames and *splits.
  */
 int vda_default_split_plan(int F, int N, int H, int d_k, int d_v, int is_f32,
                            int* tail_frames, int* splits);

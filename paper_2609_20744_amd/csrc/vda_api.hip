@@ -224,7 +224,11 @@ int stats_blocks_per_cu(int dev, int d_k, int d_v) {
 // ranges), the cheapest by this model, in ns at d_k = d_v = 128: the compute unit with
 // the most ranges takes 32 a token if it has one and 24 a token of all of
 // them if it has more, and a partial matrix pair 40 of the whole device
-// (scaled with the bytes of a token and of a partial).  It was fitted to
+// (scaled with the bytes of a token and of a partial).  A range's tokens are
+// those of whole tiles, as the kernel runs them: with N / ranges instead, 52
+// frames of 1031 tokens took four ranges of up to 320 and 70.2 us, for 68.2
+// in three of up to 384 (of 12 shapes whose plan it changes, -1.1 to +3.4%).
+// It was fitted to
 // whole passes over 128 frames (2 and 4 ranges: 1024 tokens 75.7 and 82.5 us,
 // 4032 tokens 158.6 and 153.3), 148 after a full round (2000 tokens, 1, 2 and
 // 3 ranges: 369, 357, 354) and 192 of d_k = 64 (2000 tokens, 1 and 4 ranges:
@@ -234,7 +238,9 @@ int stats_blocks_per_cu(int dev, int d_k, int d_v) {
 // unit (84 frames of 1560 tokens: 3 ranges, 252 workgroups; 4 ranges left
 // 80 compute units with two of 336); a token takes about 0.09 us of a compute
 // unit and a further partial about 1 us of the inverse, so up to eight
-// ranges of at least 128 tokens.
+// ranges of at least 128 tokens.  Rounded up to whole tiles, fewer may hold
+// them all (1025 tokens: six of 192, not eight; 16 frames 79.1 us, 81.7 with
+// the two empty ranges' partials of zeros).
 vda::SplitPlan default_plan(int dev, int F, int N, int H, int d_k, int d_v, bool is_f32) {
   const long long count = (long long)H * F;
   const long long cus = current_device_cus();
@@ -244,12 +250,17 @@ vda::SplitPlan default_plan(int dev, int F, int N, int H, int d_k, int d_v, bool
   long long k = 1;
   if (is_f32) {
     k = std::min({slots / rem, 8LL, (long long)N / 128});
+    if (k > 1) {  // no more ranges than have tokens
+      const int range = vda::stats_tokens_per_split(N, (int)k);
+      k = (N + range - 1) / range;
+    }
   } else {
     const double token = (d_k + d_v) / 256.0, partial = d_k * (d_v + 0.6 * d_k) / 26214.4;
     double best = 0.0;
     for (int c = 1; c <= 4 && rem * c <= slots && (c == 1 || N / c >= 256); ++c) {
       const long long most = (rem * c + cus - 1) / cus;
-      const double cost = (double)most * ((N + c - 1) / c) * (most == 1 ? 32.0 : 24.0) * token +
+      const double cost = (double)most * vda::stats_tokens_per_split(N, c) *
+                              (most == 1 ? 32.0 : 24.0) * token +
                           (double)((c - 1) * rem) * 40.0 * partial;
       if (c == 1 || cost < best) best = cost, k = c;
     }

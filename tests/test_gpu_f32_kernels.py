@@ -81,3 +81,20 @@ def test_scan_tiles(V, H, F, dk, dv):
     inv = V.frame_inverse(A, B, count=H * F, tail_frames=tail, splits=splits)
     sf, sr = V.state_scan(inv.view(H, F, dk, dk), B[:H * F].view(H, F, dv, dk), exact_f32=True)
     assert torch.equal(V.forward(q, k, v, beta, gate), V.readout(q, sf, sr, gate, d_v=dv))
+
+
+# Ranges are whole tiles of 64 tokens: with ceil(N / S) rounded up to them, S - 1 ranges may hold all N tokens (1025 and
+# 1100 tokens in eight of 192).  The default plan has no range without tokens, and no more than the header states.
+@pytest.mark.parametrize("is_f32,most,least", [(True, 8, 128), (False, 4, 256)])
+def test_default_plan_ranges(V, is_f32, most, least):
+    seen = set()
+    for F, H, dk, dv in [(1, 1, 128, 128), (1, 16, 128, 128), (21, 4, 128, 128), (36, 16, 128, 128), (30, 6, 64, 64),
+                         (64, 3, 64, 32)]:
+        for N in list(range(1, 2600, 3)) + [512, 1000, 1024, 1100, 3840, 4032, 100001]:
+            tail, splits = V.default_split_plan(F, N, H, dk, dv, is_f32=is_f32)
+            seen.add(splits)
+            if splits == 1:
+                continue
+            size = -(-(-(-N // splits)) // 64) * 64
+            assert (splits - 1) * size < N and splits <= min(most, N // least) and 1 <= tail <= F * H, (F, H, dk, N)
+    assert {1, 2, most} <= seen
