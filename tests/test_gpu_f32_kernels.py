@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle.vda_oracle as O
-from vda_testutil import fold_partials, to_device
+from vda_testutil import TOL_F32, fold_partials, rel_max_err, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -65,22 +65,41 @@ def test_readout(V, H, N, dk, dv):
 
 
 # The scan from fp32 operand tiles (vda_forward) does the sums of the scan from rows (the stage) in the same order, so
-# the two passes agree bit for bit: one step and no step in flight, every depth of the ring, and more heads than XCDs.
+# the two passes agree bit for bit: one step and no step in flight, every depth of the ring, and more heads than XCDs;
+# frames of one range, of three (all of whose partials the inverse loads and folds at once) and of up to eight.
 @pytest.mark.parametrize("H,F", [(1, 1), (2, 2), (1, 3), (3, 5), (9, 8)])
 @pytest.mark.parametrize("dk,dv", [(128, 128), (64, 32), (32, 128), (128, 64)])
-def test_scan_tiles(V, H, F, dk, dv):
+@pytest.mark.parametrize("N,ranges", [(33, 1), (400, 3), (1536, 8)])
+def test_scan_tiles(V, H, F, dk, dv, N, ranges):
     import torch
-    N = 33
     rng = np.random.default_rng(H + F + dk + dv)
     q, k = (to_device((x / np.linalg.norm(x, axis=-1, keepdims=True)).astype(np.float32), "f32")
             for x in (rng.standard_normal((H, F, N, dk)) for _ in range(2)))
     v = to_device(rng.standard_normal((H, F, N, dv)).astype(np.float32), "f32")
     beta, gate = (to_device(rng.random(s).astype(np.float32), "f32") for s in ((H, F, N), (H,)))
     tail, splits = V.default_split_plan(F, N, H, dk, dv, is_f32=True)
+    # (The partial round is one range per compute unit.)
+    assert splits == min(ranges, torch.cuda.get_device_properties(0).multi_processor_count // (H * F))
     A, B = V.frame_stats(k, v, beta, splits=splits, tail_frames=tail)
     inv = V.frame_inverse(A, B, count=H * F, tail_frames=tail, splits=splits)
     sf, sr = V.state_scan(inv.view(H, F, dk, dk), B[:H * F].view(H, F, dv, dk), exact_f32=True)
     assert torch.equal(V.forward(q, k, v, beta, gate), V.readout(q, sf, sr, gate, d_v=dv))
+
+
+# The whole pass with frames of three, six and eight ranges, against the oracle (the bar of the fp32 parity tests).
+@pytest.mark.parametrize("N,ranges", [(400, 3), (1100, 6), (1536, 8)])
+@pytest.mark.parametrize("dk,dv", [(128, 128), (64, 32)])
+def test_forward_ranges(V, N, ranges, dk, dv):
+    H, F = 2, 3
+    assert V.default_split_plan(F, N, H, dk, dv, is_f32=True) == (H * F, ranges)
+    rng = np.random.default_rng(N + dk)
+    q, k = ((x / np.linalg.norm(x, axis=-1, keepdims=True)).astype(np.float32)
+            for x in (rng.standard_normal((H, F, N, dk)) for _ in range(2)))
+    v = rng.standard_normal((H, F, N, dv)).astype(np.float32)
+    beta, gate = (rng.random(s).astype(np.float32) for s in ((H, F, N), (H,)))
+    y = V.forward(*(to_device(x, "f32") for x in (q, k, v, beta, gate))).double().cpu().numpy()
+    ref = O.vda_forward(*(x.astype(np.float64) for x in (q, k, v, beta, gate)))
+    assert rel_max_err(y, ref) <= TOL_F32
 
 
 # Ranges are whole tiles of 64 tokens: with ceil(N / S) rounded up to them, S - 1 ranges may hold all N tokens (1025 and

@@ -1,10 +1,10 @@
 """The block-sweep inverse where it can go wrong: every count of token-range partials that its loads group
 differently, more matrices than one round of the compute units (the waves' roles rotate), a large condition number;
-and its off-diagonal blocks are exact transposes of each other."""
+its off-diagonal blocks are exact transposes of each other; and B's partials are folded in range order."""
 import numpy as np
 import pytest
 
-from vda_testutil import from_operand_tiles, rel_max_err, to_device
+from vda_testutil import fold_partials, from_operand_tiles, rel_max_err, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -20,6 +20,7 @@ def V():
 @pytest.mark.parametrize("dk,count,tail,splits", [(32, 3, 0, 1), (32, 2, 2, 5), (64, 5, 3, 2), (64, 2, 1, 4),
                                                   (128, 3, 3, 3), (128, 2, 2, 4), (128, 2, 1, 8), (128, 530, 18, 4)])
 def test_inverse(V, dk, count, tail, splits):
+    import torch
     rng = np.random.default_rng(dk + count)
     K = rng.standard_normal((count, 2 * dk, dk)) + 2.0 * rng.standard_normal((count, 1, dk))
     K /= np.linalg.norm(K, axis=-1, keepdims=True)
@@ -38,11 +39,15 @@ def test_inverse(V, dk, count, tail, splits):
         A32[count - tail:] += parts[count + (s - 1) * tail:count + s * tail]
     ref = np.linalg.inv(np.eye(dk) + A32)
     cond = np.linalg.cond(np.eye(dk) + A32)
-    B = np.ones((nparts, 32, dk), np.float32)
+    B = rng.standard_normal((nparts, 32, dk)).astype(np.float32)
     args = dict(count=count, tail_frames=tail, splits=splits)
-    inv = V.frame_inverse(to_device(parts, "f32"), to_device(B, "f32"), **args).double().cpu().numpy()
-    tiles = V.frame_inverse(to_device(parts, "f32"), to_device(B, "f32"), tiles=True, **args)
+    Bi, Bt = to_device(B, "f32"), to_device(B, "f32")
+    inv = V.frame_inverse(to_device(parts, "f32"), Bi, **args).double().cpu().numpy()
+    tiles = V.frame_inverse(to_device(parts, "f32"), Bt, tiles=True, **args)
     tiles = from_operand_tiles(tiles, dk)
+    # Both fold B's partials into the first in range order, in fp32.
+    folded = fold_partials(torch.from_numpy(B), count, tail, splits)
+    assert torch.equal(Bi[:count].cpu(), folded) and torch.equal(Bt[:count].cpu(), folded)
     for i in range(count):
         # As the stage test's bound: fp32 elimination's error grows with the condition number.
         assert rel_max_err(inv[i], ref[i]) < 2e-6 * cond[i], (i, cond[i])
