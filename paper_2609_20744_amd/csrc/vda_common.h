@@ -14,7 +14,8 @@ constexpr float kRmsEps = 1e-6f;
 // eps); the paper states none.
 constexpr float kL2Eps = 1e-6f;
 
-// Workgroup size of every kernel: four 64-wide wavefronts, one per SIMD.
+// Workgroup size of most kernels: four 64-wide wavefronts, one per SIMD (the
+// inverse, the tiled and the fp32 scan and VDA-Prep state their own).
 constexpr int kThreads = 256;
 
 // Token tile of the frame-statistics kernels; split ranges are multiples.

@@ -401,8 +401,9 @@ __device__ __forceinline__ void run_pivot_wave(const float* A_part, int splits, 
 // Sum the token-split partials of B_t into the first one (in place, in
 // partial order) over the element range [lo, hi) of the matrix; all threads
 // of the workgroup take part.  Each thread holds up to four 16-byte pieces,
-// and the pieces of every partial are loaded together, so the whole range
-// takes one memory round trip (splits <= 4).
+// and the pieces of the first four partials are loaded together, so up to
+// four take one memory round trip (bf16 storage has no more); each further
+// one (fp32 storage plans up to eight ranges) takes another.
 __device__ __forceinline__ void fold_b_partials(float* b0, int splits, size_t lo, size_t hi,
                                                 size_t b_stride, int tid, int nthreads) {
   const size_t step = (size_t)nthreads * 4;
@@ -420,7 +421,7 @@ __device__ __forceinline__ void fold_b_partials(float* b0, int splits, size_t lo
     floatx4 sum[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) sum[e] = ((a[0][e] + a[1][e]) + a[2][e]) + a[3][e];
-    for (int s = 4; s < splits; ++s)  // more than four ranges (stage entry point only)
+    for (int s = 4; s < splits; ++s)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const size_t idx = idx0 + e * step;
