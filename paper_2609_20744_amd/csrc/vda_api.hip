@@ -539,8 +539,8 @@ hipError_t launch_forward(const ForwardCall& C, char* base, hipStream_t stream) 
   // The readout writes the true d_v channels of each head straight into out
   // (a padded head's zero channels are not stored).
   if (e == hipSuccess)
-    e = vda::launch_readout(C.is_f32, qx, S_fwd, S_rev, C.gate, F, N, H, pk, pv, d_v, go, C.out,
-                            stream);
+    e = vda::launch_readout(C.is_f32, qx, S_fwd, S_rev, C.gate, F, N, H, pk, pv, d_v, go,
+                            current_device_cus(), C.out, stream);
   return e;
 }
 
@@ -1001,7 +1001,8 @@ int vda_readout(const void* q, const float* S_fwd, const float* S_rev, const flo
       overlaps(ro, range_of(S_rev, fh * d_v * d_k * 4)) || overlaps(ro, range_of(gate, H * 4)))
     return VDA_ERR_OVERLAP;
   return hip_status(vda::launch_readout(is_f32 != 0, q, S_fwd, S_rev, gate, F, N, H, d_k, d_v,
-                                        d_v, vda::GatherOptions(), out, stream));
+                                        d_v, vda::GatherOptions(), current_device_cus(), out,
+                                        stream));
 }
 
 }  // extern "C"

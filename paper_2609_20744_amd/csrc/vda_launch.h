@@ -130,9 +130,11 @@ struct GatherOptions {
 // d_v_norm: the true number of value channels, which RMSNorm averages over
 // and out holds per head (d_v, or fewer when the trailing value channels of
 // the padded heads are zero padding: only the first d_v_norm are written).
+// cus: compute units of the current device.
 hipError_t launch_readout(bool is_f32, const void* q, const float* S_fwd, const float* S_rev,
                           const float* gate, int F, int N, int H, int d_k, int d_v,
-                          int d_v_norm, const GatherOptions& g, void* out, hipStream_t stream);
+                          int d_v_norm, const GatherOptions& g, int cus, void* out,
+                          hipStream_t stream);
 
 // The prompt state from its frame's reduced statistics: S = B Inv (joint
 // rule; Inv != null) or S = B * scale (frozen rule).  B [H][pv][pk], Inv

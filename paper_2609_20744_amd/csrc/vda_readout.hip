@@ -461,9 +461,8 @@ inline int readout_chunks(long long fh_count, int N) {
 // even load over the compute units: a launch takes about as many 64-token
 // steps as the busiest one has, and something like one more per workgroup
 // for the state prologue.  The smallest count that minimises it is used (84
-// frames of 1560 tokens: 3 workgroups, 252 in all).
-inline int readout_f32_chunks(long long fh_count, int N) {
-  const long long cus = 256;
+// frames of 1560 tokens on 256 compute units: 3 workgroups, 252 in all).
+inline int readout_f32_chunks(long long fh_count, int N, int cus) {
   const int steps = (N + 63) / 64;
   int best = 1;
   long long best_cost = -1;
@@ -477,12 +476,12 @@ inline int readout_f32_chunks(long long fh_count, int N) {
 template <int DK, int DV>
 hipError_t launch_readout_t(bool is_f32, const void* q, const float* S_fwd, const float* S_rev,
                             const float* gate, int F, int N, int H, int d_v_norm,
-                            const GatherOptions& go, void* out, hipStream_t stream) {
+                            const GatherOptions& go, int cus, void* out, hipStream_t stream) {
   const long long fh_count = (long long)H * F;
   const bool genout = go.out_heads > 1 || d_v_norm != DV || go.q_heads > 1 || go.q_l2;
   const int ql2 = go.q_l2 ? 1 : 0;
   if (is_f32) {
-    const int chunks = readout_f32_chunks(fh_count, N);
+    const int chunks = readout_f32_chunks(fh_count, N, cus);
     const dim3 grid((unsigned)(fh_count * chunks));
 #define VDA_READOUT_F32(TG)                                                                      \
   hipLaunchKernelGGL((readout_f32_kernel<DK, DV, TG>), grid, dim3(kThreads), 0, stream,          \
@@ -528,11 +527,11 @@ hipError_t launch_readout_t(bool is_f32, const void* q, const float* S_fwd, cons
 
 hipError_t launch_readout(bool is_f32, const void* q, const float* S_fwd, const float* S_rev,
                           const float* gate, int F, int N, int H, int d_k, int d_v, int d_v_norm,
-                          const GatherOptions& go, void* out, hipStream_t stream) {
-#define VDA_READOUT_CASE(DKV, DVV)                                                            \
-  if (d_k == DKV && d_v == DVV)                                                               \
-    return launch_readout_t<DKV, DVV>(is_f32, q, S_fwd, S_rev, gate, F, N, H, d_v_norm, go, out, \
-                                      stream);
+                          const GatherOptions& go, int cus, void* out, hipStream_t stream) {
+#define VDA_READOUT_CASE(DKV, DVV)                                                             \
+  if (d_k == DKV && d_v == DVV)                                                                \
+    return launch_readout_t<DKV, DVV>(is_f32, q, S_fwd, S_rev, gate, F, N, H, d_v_norm, go, cus, \
+                                      out, stream);
   VDA_READOUT_CASE(32, 32) VDA_READOUT_CASE(32, 64) VDA_READOUT_CASE(32, 128)
   VDA_READOUT_CASE(64, 32) VDA_READOUT_CASE(64, 64) VDA_READOUT_CASE(64, 128)
   VDA_READOUT_CASE(128, 32) VDA_READOUT_CASE(128, 64) VDA_READOUT_CASE(128, 128)
