@@ -53,7 +53,8 @@ struct ScanOptions {
 // Steps a3/a4, Eq. A.1: forward and reverse state scans (exact fp32 products,
 // or split-bf16 products with fp32 accumulation).  Mat is Inv_t (joint rule)
 // or A_t (frozen rule), symmetric; f32_tiles (exact_f32 and joint rule only):
-// Inv_t as fp32 operand tiles (InvLayout::kF32Tiles), not by rows.
+// Inv_t as fp32 operand tiles (InvLayout::kF32Tiles), not by rows.  Without
+// exact_f32 no options are taken (the whole bf16 passes run on the tiled scan).
 hipError_t launch_state_scan(bool exact_f32, const float* Mat, const float* Bm, int F, int H,
                              int d_k, int d_v, const ScanOptions& o, float* S_fwd, float* S_rev,
                              hipStream_t stream, bool f32_tiles = false);

@@ -66,7 +66,7 @@ template <int DK, int DV, bool TOKGATE, bool GENOUT>
 __global__ __launch_bounds__(kThreads, 2)
 void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict__ S_fwd,
                          const float* __restrict__ S_rev, const float* __restrict__ gate,
-                         int F, int N, int chunks, int tokens_per_chunk, unsigned nwg,
+                         int F, int N, int chunks, unsigned nwg,
                          int dvo, int oh, int qh, int ql2, const float* __restrict__ alpha,
                          int wchunk, int wradius, int woffset, const uint16_t* __restrict__ gtok,
                          uint16_t* __restrict__ out) {
@@ -497,27 +497,23 @@ hipError_t launch_readout_t(bool is_f32, const void* q, const float* S_fwd, cons
     return hipGetLastError();
   }
   const int chunks = readout_chunks(fh_count, N);
-  int tpc = (N + chunks - 1) / chunks;
-  tpc = ((tpc + 63) / 64) * 64;
   const dim3 grid((unsigned)(fh_count * chunks));
-#define VDA_READOUT_LAUNCH(TG, GO)                                                                 \
-  hipLaunchKernelGGL((readout_bf16_kernel<DK, DV, TG, GO>), grid, dim3(kThreads), 0, stream,       \
-                       static_cast<const uint16_t*>(q), S_fwd, S_rev, gate, F, N, chunks, tpc,    \
-                       (unsigned)(fh_count * chunks), d_v_norm, go.out_heads, go.q_heads, ql2,     \
-                       go.alpha, go.chunk,                                                         \
-                       go.radius,                                                                  \
-                       go.offset, static_cast<const uint16_t*>(go.gate_tokens),                    \
-                       static_cast<uint16_t*>(out));
+#define VDA_READOUT_LAUNCH(TG, GO)                                                               \
+  hipLaunchKernelGGL((readout_bf16_kernel<DK, DV, TG, GO>), grid, dim3(kThreads), 0, stream,     \
+                     static_cast<const uint16_t*>(q), S_fwd, S_rev, gate, F, N, chunks, grid.x,  \
+                     d_v_norm, go.out_heads, go.q_heads, ql2, go.alpha, go.chunk, go.radius,     \
+                     go.offset, static_cast<const uint16_t*>(go.gate_tokens),                    \
+                     static_cast<uint16_t*>(out))
   if (go.gate_tokens != nullptr) {
     if (genout) {
-      VDA_READOUT_LAUNCH(true, true)
+      VDA_READOUT_LAUNCH(true, true);
     } else {
-      VDA_READOUT_LAUNCH(true, false)
+      VDA_READOUT_LAUNCH(true, false);
     }
   } else if (genout) {
-    VDA_READOUT_LAUNCH(false, true)
+    VDA_READOUT_LAUNCH(false, true);
   } else {
-    VDA_READOUT_LAUNCH(false, false)
+    VDA_READOUT_LAUNCH(false, false);
   }
 #undef VDA_READOUT_LAUNCH
   return hipGetLastError();

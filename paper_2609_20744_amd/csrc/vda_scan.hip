@@ -36,8 +36,17 @@ __device__ __forceinline__ void split_bf16x8(const float (&x)[8], bf16x8& hi, bf
   }
 }
 
-// The exact fp32 scan (fp32 storage path); DECAY and FROZEN as described at
-// scan_bf16_kernel below.  As in the tiled scan of the bf16 path the product
+// The exact fp32 scan (fp32 storage path).  Options of the full operator
+// (template switches, so the core path carries none of their work):
+//   DECAY  - the entering state is decayed, Sbar = S Diag(alpha_t), before
+//            the frame's write (Eq. 5 / A.1 with alpha);
+//   FROZEN - the frozen-state additive rule with 1/sqrt(U) key scaling,
+//            S_t = Sbar_t (I - A_t / U) + B_t / sqrt(U) (Eq. 3c): the product
+//            takes I - A_t / U, formed from A_t, and the write B_t / sqrt(U)
+//            is added after it, that is at the start of the next step (B is
+//            loaded one frame late).
+// It may start from a text state, S_T / 2 (Eq. 1b).
+// As in the tiled scan of the bf16 path the product
 // is formed transposed, Inv_t x^T: its result leaves a lane four
 // consecutive columns of one state row, which are its B-operand of the next
 // product (v_mfma_f32_16x16x4_f32, lane group lg of k chunk c supplying k =
@@ -347,25 +356,14 @@ __device__ __forceinline__ void scan_mfma_phase(const uint16_t* __restrict__ xhi
 // two lane groups of each 32-lane LDS pass then fall on distinct banks in
 // both kinds of read.
 //
-// Options of the full operator (template switches, so the core path carries
-// none of their work):
-//   DECAY  - the entering state is decayed, Sbar = S Diag(alpha_t), before
-//            the frame's write (Eq. 5 / A.1 with alpha); alpha_t reaches the
-//            row-wise phase through a small LDS row written one step ahead.
-//   FROZEN - the frozen-state additive rule with 1/sqrt(U) key scaling,
-//            S_t = Sbar_t (I - A_t / U) + B_t / sqrt(U) (Eq. 3c): the staged
-//            matrix is I - A_t / U, built from A_t on the way into LDS, and
-//            the write B_t / sqrt(U) is added after the product, that is at
-//            the start of the next step (B is loaded one frame late), so the
-//            state kept between steps is S_t - B_t / sqrt(U).  (Not launched:
-//            with bf16 storage the frozen rule runs on the tiled scan.)
-// Both scans may start from a text state: S_T / 2 (Eq. 1b).
-template <int DK, bool FROZEN, bool DECAY>
+// It serves the stage entry point, which takes Inv_t by rows and none of the
+// full operator's options: with bf16 storage the whole passes run on the tiled
+// scan.
+template <int DK>
 __global__ __launch_bounds__(kThreads)
 void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ Bm,
-                      const float* __restrict__ alpha, const float* __restrict__ text_state,
-                      int F, int DV, unsigned nwg, float inv_u, float inv_sqrt_u,
-                      float* __restrict__ S_fwd, float* __restrict__ S_rev) {
+                      int F, int DV, unsigned nwg, float* __restrict__ S_fwd,
+                      float* __restrict__ S_rev) {
   constexpr int XLD = DK + 4;        // LDS row stride (floats)
   constexpr int VW = DK >= 64 ? 4 : 2;  // floats per access in the row-wise phase
   constexpr int NG = DK / (16 * VW);    // accesses per thread in the row-wise phase
@@ -375,7 +373,6 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
   __shared__ __align__(16) float ivs[(DK + 1) * XLD];  // matrix image, plus a dummy row
   __shared__ __align__(16) float xs[2][16 * XLD];
   __shared__ __align__(16) uint16_t xsp[2][16 * PLD];   // bf16 hi / lo planes of the block
-  __shared__ __align__(16) float alds[DECAY ? DK : 4];  // alpha of the coming step
 
   const int nrb = DV / 16;
   const unsigned L = xcd_grouped_id(blockIdx.x, nwg);
@@ -396,13 +393,7 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
   const int pc = (tid & 15) * VW;
 
   const size_t mat_b = (size_t)DV * DK;  // one B / state matrix
-  // Initial state: S_T / 2 (rows of this block), or zero.
-  for (int i = tid; i < 16 * XLD; i += kThreads) {
-    const int r = i / XLD, c = i % XLD;
-    xs[0][i] = text_state != nullptr && c < DK
-                   ? 0.5f * text_state[(size_t)hb * mat_b + (size_t)(rb * 16 + r) * DK + c]
-                   : 0.f;
-  }
+  for (int i = tid; i < 16 * XLD; i += kThreads) xs[0][i] = 0.f;  // the initial state
 
   float* Sout = dir == 0 ? S_fwd : S_rev;
   const size_t row_off = (size_t)(rb * 16 + pr) * DK + pc;
@@ -413,8 +404,6 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
   // B of this head, range-checked (frames outside [0, F) read as zero).
   const __amdgpu_buffer_rsrc_t brsrc =
       make_rsrc(Bm + (size_t)hb * F * mat_b, (uint32_t)(F * mat_b * sizeof(float)));
-  const __amdgpu_buffer_rsrc_t arsrc =
-      make_rsrc(DECAY ? alpha + (size_t)hb * F * DK : Bm, DECAY ? (uint32_t)(F * DK * 4) : 0u);
 
   auto frame_of = [&](int step) { return dir == 0 ? step : F - 1 - step; };
 
@@ -437,20 +426,14 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
   // indices only).
   u32x4 ir0[CPT], ir1[CPT];
   float bs0[NG][VW], bs1[NG][VW];
-  u32x4 al0, al1;  // alpha_t, columns 4 tid .. 4 tid + 3 (threads tid < DK / 4)
-  auto load_step = [&](int step, u32x4 (&ir)[CPT], float (&bb)[NG][VW], u32x4& al) {
+  auto load_step = [&](int step, u32x4 (&ir)[CPT], float (&bb)[NG][VW]) {
     const int frame = frame_of(step);
-    // The write added in this step: B of this frame (joint rule) or of the
-    // previous one (frozen rule; none before the first frame).
-    const int bframe = FROZEN ? frame_of(step - 1) : frame;
-    const bool bin = (unsigned)bframe < (unsigned)F;
     // B rows first (they are needed earlier in the step than the matrix),
     // and everything through buffer loads, which the compiler keeps in
     // program order.
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-      const uint32_t off =
-          bin ? (uint32_t)(((size_t)bframe * mat_b + row_off + g * 16 * VW) * 4u) : kOutOfRange;
+      const uint32_t off = (uint32_t)(((size_t)frame * mat_b + row_off + g * 16 * VW) * 4u);
       if constexpr (VW == 4) {
         const u32x4 x =
             __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(brsrc, (int)off, 0, 0));
@@ -463,10 +446,6 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
         bb[g][1] = __uint_as_float(x[1]);
       }
     }
-    if constexpr (DECAY) {
-      const uint32_t off = tid < DK / 4 ? (uint32_t)(frame * DK + 4 * tid) * 4u : kOutOfRange;
-      al = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(arsrc, (int)off, 0, 0));
-    }
     const size_t fh = (size_t)hb * F + frame;
     const __amdgpu_buffer_rsrc_t irsrc = make_rsrc(Mat + fh * (DK * DK), DK * DK * 4u);
 #pragma unroll
@@ -475,26 +454,13 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
           u32x4, __builtin_amdgcn_raw_buffer_load_b128(irsrc, (int)goff[e], 0, 0));
   };
 
-  // The staged matrix: Inv_t as loaded (joint rule), or I - A_t / U from the
-  // loaded A_t (frozen rule).
   auto stage = [&](const u32x4 (&ir)[CPT]) {
 #pragma unroll
-    for (int e = 0; e < CPT; ++e) {
-      u32x4 w = ir[e];
-      if constexpr (FROZEN) {
-        const int elem = (int)(goff[e] / 4u);
-        const int row = elem / DK, col = elem % DK;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          w[c] = __float_as_uint((row == col + c ? 1.0f : 0.0f) - __uint_as_float(w[c]) * inv_u);
-      }
-      reinterpret_cast<u32x4*>(ivs)[loff[e]] = w;
-    }
+    for (int e = 0; e < CPT; ++e) reinterpret_cast<u32x4*>(ivs)[loff[e]] = ir[e];
   };
 
   int cur = 0;
-  auto step_body = [&](int step, u32x4 (&ir)[CPT], float (&bb)[NG][VW], u32x4& al,
-                       const u32x4& al_next) {
+  auto step_body = [&](int step, u32x4 (&ir)[CPT], float (&bb)[NG][VW]) {
     // Frame index within the head; past the end it is out of the buffer
     // range (>= F forward, negative and so huge as unsigned in reverse).
     const int frame = dir == 0 ? step : F - 1 - step;
@@ -515,24 +481,14 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
           v[0] = xv.x;
           v[1] = xv.y;
         }
-        if constexpr (FROZEN) {  // the previous frame's write, B / sqrt(U)
-#pragma unroll
-          for (int c = 0; c < VW; ++c) v[c] += bb[g][c] * inv_sqrt_u;
-        }
         if constexpr (VW == 4)
           store_b128(srsrc, off + g * 64u * VW,
                      u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
                            __float_as_uint(v[3])});
         else
           store_b64(srsrc, off + g * 64u * VW, make_uint2(__float_as_uint(v[0]), __float_as_uint(v[1])));
-        if constexpr (DECAY) {
 #pragma unroll
-          for (int c = 0; c < VW; ++c) v[c] *= alds[pc + g * 16 * VW + c];
-        }
-        if constexpr (!FROZEN) {
-#pragma unroll
-          for (int c = 0; c < VW; ++c) v[c] += bb[g][c];
-        }
+        for (int c = 0; c < VW; ++c) v[c] += bb[g][c];
         // The product's A-operand, split once here into bf16 hi and lo
         // (instead of by each of the four waves).
         uint32_t hw[VW / 2], lw[VW / 2];
@@ -554,14 +510,9 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
       }
     }
     lds_barrier();
-    // alpha of the next step, read by its row-wise phase (after the next
-    // barrier); this step's reads of alds are complete.
-    if constexpr (DECAY) {
-      if (tid < DK / 4) reinterpret_cast<u32x4*>(alds)[tid] = al_next;
-    }
     // Always refill (past the end: a clamped, unused frame) so no branch
     // hides the loads from the wait-count bookkeeping.
-    load_step(min(step + 2, F - 1), ir, bb, al);
+    load_step(min(step + 2, F - 1), ir, bb);
     switch (wave) {  // wave-uniform
       case 0: scan_mfma_phase<DK, 0>(xsp[0], xsp[1], xs[cur ^ 1], ivs, li, lg); break;
       case 1: scan_mfma_phase<DK, 1>(xsp[0], xsp[1], xs[cur ^ 1], ivs, li, lg); break;
@@ -573,48 +524,37 @@ void scan_bf16_kernel(const float* __restrict__ Mat, const float* __restrict__ B
 
   // Issue the ring in slot order (pinned against rescheduling) so slot 0 is
   // the oldest load on loop entry.
-  load_step(0, ir0, bs0, al0);
+  load_step(0, ir0, bs0);
   __builtin_amdgcn_sched_barrier(0);
-  load_step(min(1, F - 1), ir1, bs1, al1);
+  load_step(min(1, F - 1), ir1, bs1);
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (DECAY) {  // alpha of step 0
-    if (tid < DK / 4) reinterpret_cast<u32x4*>(alds)[tid] = al0;
-  }
   // The step count is padded to an even number; a padded step (step >= F)
   // reads a clamped frame and its stores are dropped, so the loop body has
   // no early exit.
   for (int step0 = 0; step0 < F; step0 += 2) {
-    step_body(step0, ir0, bs0, al0, al1);
-    step_body(step0 + 1, ir1, bs1, al1, al0);
+    step_body(step0, ir0, bs0);
+    step_body(step0 + 1, ir1, bs1);
   }
 }
 
 template <int DK, bool FROZEN, bool DECAY>
-hipError_t launch_scan_v(bool exact_f32, const float* Mat, const float* Bm, int F, int H, int d_v,
-                         const ScanOptions& o, bool f32_tiles, float* S_fwd, float* S_rev,
-                         hipStream_t stream) {
+hipError_t launch_scan_f32(const float* Mat, const float* Bm, int F, int H, int d_v,
+                           const ScanOptions& o, bool f32_tiles, float* S_fwd, float* S_rev,
+                           hipStream_t stream) {
   const unsigned nwg = (unsigned)H * 2u * (unsigned)(d_v / 16);
   const float inv_u = FROZEN ? 1.0f / (float)o.tokens : 0.0f;
   const float inv_sqrt_u = FROZEN ? 1.0f / sqrtf((float)o.tokens) : 0.0f;
-  if (exact_f32) {
-    const dim3 block(DK == 32 ? 128 : 256);
-    if (f32_tiles) {
-      if constexpr (FROZEN) return hipErrorInvalidValue;
-      else
-        hipLaunchKernelGGL((scan_f32_kernel<DK, false, DECAY, true>), dim3(nwg), block, 0, stream,
-                           Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd,
-                           S_rev);
-    } else {
-      hipLaunchKernelGGL((scan_f32_kernel<DK, FROZEN, DECAY, false>), dim3(nwg), block, 0, stream,
-                         Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd,
-                         S_rev);
-    }
-  } else {
-    // With bf16 storage the frozen rule runs on the tiled scan (map form).
+  const dim3 block(DK == 32 ? 128 : 256);
+  if (f32_tiles) {
     if constexpr (FROZEN) return hipErrorInvalidValue;
     else
-      hipLaunchKernelGGL((scan_bf16_kernel<DK, false, DECAY>), dim3(nwg), dim3(kThreads), 0, stream,
-                         Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd, S_rev);
+      hipLaunchKernelGGL((scan_f32_kernel<DK, false, DECAY, true>), dim3(nwg), block, 0, stream,
+                         Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd,
+                         S_rev);
+  } else {
+    hipLaunchKernelGGL((scan_f32_kernel<DK, FROZEN, DECAY, false>), dim3(nwg), block, 0, stream,
+                       Mat, Bm, o.alpha, o.text_state, F, d_v, nwg, inv_u, inv_sqrt_u, S_fwd,
+                       S_rev);
   }
   return hipGetLastError();
 }
@@ -624,15 +564,18 @@ hipError_t launch_scan_t(bool exact_f32, const float* Mat, const float* Bm, int 
                          const ScanOptions& o, bool f32_tiles, float* S_fwd, float* S_rev,
                          hipStream_t stream) {
   const bool decay = o.alpha != nullptr;
-  if (o.frozen)
-    return decay ? launch_scan_v<DK, true, true>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
-                                            stream)
-                 : launch_scan_v<DK, true, false>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
-                                            stream);
-  return decay ? launch_scan_v<DK, false, true>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
-                                            stream)
-               : launch_scan_v<DK, false, false>(exact_f32, Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev,
-                                            stream);
+  if (!exact_f32) {
+    if (o.frozen || decay || o.text_state != nullptr) return hipErrorInvalidValue;
+    const unsigned nwg = (unsigned)H * 2u * (unsigned)(d_v / 16);
+    hipLaunchKernelGGL(scan_bf16_kernel<DK>, dim3(nwg), dim3(kThreads), 0, stream, Mat, Bm, F, d_v,
+                       nwg, S_fwd, S_rev);
+    return hipGetLastError();
+  }
+#define VDA_SCAN_F32(FROZEN, DECAY) \
+  launch_scan_f32<DK, FROZEN, DECAY>(Mat, Bm, F, H, d_v, o, f32_tiles, S_fwd, S_rev, stream)
+  if (o.frozen) return decay ? VDA_SCAN_F32(true, true) : VDA_SCAN_F32(true, false);
+  return decay ? VDA_SCAN_F32(false, true) : VDA_SCAN_F32(false, false);
+#undef VDA_SCAN_F32
 }
 
 }  // namespace
