@@ -289,14 +289,21 @@ Workspace workspace_layout(int F, int H, int d_k, int d_v, vda::SplitPlan plan) 
 }
 
 // Whether the chunk-wise scans beat the frame-by-frame scan for a chunked
-// window, by a cost model fitted per key width to measurements on MI355X
-// (both scans alone, d_v = d_k, chunks of five after one anchor, at 16 heads
-// x 36 frames and 7 heads x 100 frames).  The frame scan costs about
+// window, by a cost model per key width.  The frame scan costs about
 // a * F + b us; the chunk-wise scans s * (5 * chunk + 13) us per round of
 // 2 * H * C compose workgroups over the compute units plus g us per chunk.
-//   d_k = 128: frame 43.4 / 97.6 us, chunk-wise 56.6 / 90.1 us
-//   d_k =  64: frame 18.5 / 46.4 us, chunk-wise 15.1 / 24.3 us
-//   d_k =  32: frame 13.6 / 33.7 us, chunk-wise 10.8 / 14.5 us
+// The constants were fitted to an earlier form of the tiled scan (both scans
+// alone, d_v = d_k, chunks of five after one anchor, no decay, at 16 heads x
+// 36 frames / 7 heads x 100 frames; in brackets today's):
+//   d_k = 128: frame 43.4 / 97.6 (38.2 / 86.7) us, chunk-wise 56.6 / 90.1 (52.8 / 88.3) us
+//   d_k =  64: frame 18.5 / 46.4 (16.6 / 39.8) us, chunk-wise 15.1 / 24.3 (14.5 / 23.8) us
+//   d_k =  32: frame 13.6 / 33.7 (10.6 / 25.7) us, chunk-wise 10.8 / 14.5 (8.6 / 14.0) us
+// Of 1400 whole passes over frames of 128 tokens (1 - 24 heads, 20 - 100
+// frames, chunks of 2 - 10, every pair of 64 and 128 channels and 32 x 32,
+// with and without decay) the model now takes the slower scan by more than 1%
+// of the pass in 253: 210 that stay with the frame scan (up to half of such a
+// short pass; most with fewer than 16 heads of d_k = 128 or 32) and 43 that
+// compose.
 bool chunked_scan_pays(int F, int H, int d_k, int chunk, int offset) {
   const int C = vda::chunk_count(F, chunk, offset);
   if (C < 2) return false;

@@ -56,10 +56,10 @@ hipError_t launch_frame_inverse(const float* A_part, float* B_part, SplitPlan pl
   // partials (a quarter of the matrix each, one memory round trip).
   const unsigned extra = splits > 1 ? 4u * (unsigned)plan.tail : 0u;
   const dim3 grid((unsigned)count + extra);
-#define VDA_INVERSE(DK, OUT)                                                                      \
-  hipLaunchKernelGGL((inverse_kernel<DK, (int)InvLayout::OUT>), grid,                       \
-                     dim3(inv::inverse_threads(DK)), 0, stream, A_part, first_split, splits, extra, part_stride, Inv, B_part, b_mat, \
-                     b_stride)
+#define VDA_INVERSE(DK, OUT)                                                                 \
+  hipLaunchKernelGGL((inverse_kernel<DK, (int)InvLayout::OUT>), grid,                        \
+                     dim3(inv::inverse_threads(DK)), 0, stream, A_part, first_split, splits, \
+                     extra, part_stride, Inv, B_part, b_mat, b_stride)
 #define VDA_INVERSE_DK(DK)                                                  \
   if (out == InvLayout::kBf16Tiles)                                         \
     VDA_INVERSE(DK, kBf16Tiles);                                            \

@@ -35,9 +35,9 @@ hipError_t launch_frame_stats(bool is_f32, const void* k, const void* v, const f
                               float* A_part, float* B_part, hipStream_t stream,
                               bool lower_only = false);
 
-// Step a2, Eq. 5: Inv = (I + sum of A partials)^{-1}, in layout `out`; also folds the B partials of every
-// split frame into its first partial.  It reads only A_t's blocks on and
-// below the diagonal.
+// Step a2, Eq. 5: Inv = (I + sum of A partials)^{-1}, in layout `out`; also
+// folds the B partials of every split frame into its first partial.  It reads
+// only A_t's blocks on and below the diagonal.
 hipError_t launch_frame_inverse(const float* A_part, float* B_part, SplitPlan plan,
                                 long long count, int d_k, int d_v, InvLayout out, float* Inv,
                                 hipStream_t stream);

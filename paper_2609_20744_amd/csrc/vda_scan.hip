@@ -15,7 +15,7 @@
 // they share Inv_t in its L2.
 //
 // Products: with fp32 storage (scan_f32_kernel), v_mfma_f32_16x16x4_f32
-// (exact fp32 products).  With bf16 storage (scan_bf16_kernel, which also
+// (exact fp32 products).  With bf16 products (scan_bf16_kernel, which also
 // stages Inv_t through LDS, see there), each fp32 operand x is split into
 // bf16 hi = bf16(x) and lo = bf16(x - hi), and the product is hi*hi + hi*lo +
 // lo*hi on v_mfma_f32_16x16x32_bf16 with fp32 accumulation (about 16
@@ -334,7 +334,7 @@ __device__ __forceinline__ void scan_mfma_phase(const uint16_t* __restrict__ xhi
   }
 }
 
-// The split-bf16 scan (bf16 storage path).  The recurrence, the work split
+// The split-bf16 scan from Inv_t by rows.  The recurrence, the work split
 // (one 16-row block of one chain per workgroup) and the products are those
 // of scan_f32_kernel; the difference is how Inv_t reaches the matrix cores.
 // Per frame the workgroup copies only the blocks of Inv_t on and above the

@@ -311,12 +311,13 @@ void stats_bf16_kernel(const uint16_t* __restrict__ K, const uint16_t* __restric
 // float of the natural-layout tile in LDS ([token][k, v channels], row
 // stride 16 mod 64 floats: the four tokens of a read lie on different banks).
 // beta * k is the k operand times the lane's token's beta, so no second
-// image of the keys is kept.  A tile is 16 tokens (32 for 32-channel heads),
-// the next one in flight in registers.  The sums run in two levels, 256
-// tokens in the products' accumulators and those into a second set of
-// registers: a single chain's rounding error grows with the tokens of the
-// range (whole pass against 64 bits at 4 heads x 21 frames x 1560 tokens,
-// 520 a range: 9.2e-7 with one chain, 8.2e-7 for ranges of 390).
+// image of the keys is kept.  A tile is 32 tokens, the next one in flight in
+// registers.  The sums run in two levels, 256 tokens in the products'
+// accumulators and those into a second set of registers: a single chain's
+// rounding error grows with the tokens of the range (whole pass against 64
+// bits at 4 heads x 21 frames x 1560 tokens: 9.2e-7 with one chain and ranges
+// of up to 576 tokens, 6.6e-7 so; 8.2e-7 for one chain on the vector ALUs and
+// ranges of up to 448).
 // What bounds it: the fp32 matrix rate (25 products of 32 cycles per wave
 // and four tokens at d = 128, A_t's upper triangle and B_t): 48 us of the
 // 75 us it takes at 4 heads x 21 frames x 1560 tokens x 128 channels; the
@@ -516,10 +517,19 @@ int blocks_per_cu_t() {
 // read once from displacing what the next steps read (the partials written
 // here, later the operand tiles and B_t) from the 256 MB last-level cache,
 // and needs no victims evicted for it: from a quarter of that cache on.
-// Below it, where inputs used again may still lie there, it costs a little
-// (8 heads x 16 frames x 1024 tokens, d = 64, 34 MB: 40.5 -> 41.3 us a pass;
-// d = 128, 67 MB: 86.4 -> 81.9; 24 x 21 x 1560: 248 -> 228, the statistics
-// alone 98 -> 80).
+// What it gives depends on where the inputs lie, so the line is a compromise
+// (us a pass, default -> nt, 8 heads x 16 frames, d = 128, MB of k and v):
+//   MB   the same buffers again   after VDA-Prep   after a 300 MB fill
+//   32       63.1 -> 64.4           74.0 -> 74.4       75.9 -> 73.7
+//   48       65.2 -> 67.3           76.6 -> 76.5       80.4 -> 80.1
+//   64       70.8 -> 73.5           80.4 -> 80.2       89.8 -> 87.2
+//   80       77.3 -> 80.6           90.7 -> 88.5      103.9 -> 98.7
+// Between 16 x 32 frames of d = 64: 56 MB 52.8 -> 54.2, 59.0 -> 58.9, 70.1 ->
+// 66.5; 72 MB 58.6 -> 60.3, 67.5 -> 65.6, 80.3 -> 74.2.  Straight after the
+// kernel that wrote them, as in a model, nt is no better below 64 MB and
+// better above, where the same buffers used again soon no longer fit the
+// cache either (24 x 21 x 1560, 403 MB: 248 -> 228, the statistics alone 98 ->
+// 80).
 inline bool use_stream(long long kv_bytes) { return kv_bytes >= (64LL << 20); }
 
 template <int DK, int DV>
