@@ -91,12 +91,12 @@ const char* vda_status_string(int status);
  * on failure).  Cached buffers are kept until vda_release_workspace frees
  * them or the process ends.
  * A 16-channel d_k or d_v is run as a 32-channel head whose extra channels
- * are zero: q, k (and v) are copied into padded workspace buffers, zero
+ * are zero: q and k, or v, are copied into padded workspace buffers, zero
  * channels leave A_t, B_t, the states and the readout unchanged, RMSNorm
- * averages over the true d_v, and the padded output is copied back into
- * out.  The workspace then also holds those padded copies (the formula above
- * with 32 for the padded dimension, plus 2*H*F*N*32 elements of the storage
- * type per padded dimension).
+ * averages over the true d_v, and only the true channels of out are written.
+ * The workspace then also holds those padded copies (the formula above with
+ * 32 for the padded dimension, plus H*F*N*32 elements of the storage type per
+ * padded input).
  */
 int vda_forward(const void* q, const void* k, const void* v,
                 const float* beta, const float* gate,

@@ -354,7 +354,7 @@ struct ForwardCall {
   size_t es = 0, tok = 0;
   vda::SplitPlan plan{0, 1};
   Workspace w;
-  size_t qk_pad = 0, v_pad = 0, a_pad = 0, t_pad = 0, t_tmp = 0, g_pad = 0, c_ws = 0;
+  size_t qk_pad = 0, v_pad = 0, a_pad = 0, t_pad = 0, t_tmp = 0, c_ws = 0;
   size_t ws_bytes = 0;
 };
 
@@ -442,9 +442,8 @@ void plan_forward(bool is_f32, const void* q, const void* k, const void* v, cons
   C.a_pad = pk != d_k && o.alpha ? round_up((size_t)H * F * pk * 4, 256) : 0;
   C.t_pad = pad_any && o.text_state ? round_up((size_t)H * pv * pk * 4, 256) : 0;
   C.t_tmp = pad_any && o.text_state ? round_up((size_t)H * d_v * pk * 4, 256) : 0;
-  C.g_pad = o.gate_tokens && pv != d_v ? round_up(tok * pv * es, 256) : 0;
   C.ws_bytes = round_up(C.w.total, 256) + 2 * C.qk_pad + C.v_pad + C.a_pad + C.t_pad +
-               C.t_tmp + C.g_pad + C.c_ws;
+               C.t_tmp + C.c_ws;
 }
 
 // Enqueues a planned forward call with its workspace at `base` (at least
@@ -482,14 +481,7 @@ hipError_t launch_forward(const ForwardCall& C, char* base, hipStream_t stream) 
     vx = vp;
   }
   char* opt_base = pad_base + 2 * C.qk_pad + C.v_pad;
-  void* chunk_work = opt_base + C.a_pad + C.t_pad + C.t_tmp + C.g_pad;
-  const void* gt_x = o.gate_tokens;
-  if (C.g_pad && e == hipSuccess) {  // output gates [tok][d_v] -> [tok][32], zero channels added
-    void* gp = opt_base + C.a_pad + C.t_pad + C.t_tmp;
-    e = vda::launch_pad_rows(o.gate_tokens, gp, (long long)tok, (int)(d_v * es), (int)(pv * es),
-                             stream);
-    gt_x = gp;
-  }
+  void* chunk_work = opt_base + C.a_pad + C.t_pad + C.t_tmp;
   if (C.a_pad && e == hipSuccess) {  // alpha [H][F][d_k] -> [H][F][32]
     float* ap = reinterpret_cast<float*>(opt_base);
     e = vda::launch_pad_rows(o.alpha, ap, (long long)H * F, d_k * 4, pk * 4, stream);
@@ -539,7 +531,7 @@ hipError_t launch_forward(const ForwardCall& C, char* base, hipStream_t stream) 
   go.chunk = o.window_chunk;
   go.radius = o.window_radius;
   go.offset = o.window_offset;
-  go.gate_tokens = gt_x;
+  go.gate_tokens = o.gate_tokens;
   go.out_heads = o.out_heads > 0 ? o.out_heads : 1;
   go.q_heads = o.q_heads > 0 ? o.q_heads : 1;
   go.q_l2 = o.q_heads > 0;

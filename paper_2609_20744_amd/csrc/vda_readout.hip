@@ -165,21 +165,25 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
     for (int kb = 0; kb < KB; ++kb)
       qv[kb] = *reinterpret_cast<const uint4*>(qbase + (size_t)row * qrs + kb * 32 + lg * 8);
   };
-  // TOKGATE: the output gate of the same groups, whole rows in the stores'
-  // layout (rows past the frame read as zero); read once, so streamed (nt).
+  // TOKGATE: the output gate of the same groups, whole rows of the true dvw
+  // channels in the stores' layout (rows past the frame and a padded head's
+  // channels read as zero); read once, so streamed (nt).  (From a copy padded
+  // to 32 channels, as the other inputs of 16-channel heads are, those heads
+  // took 100 us a pass at 12 heads x 40 frames x 1000 tokens, 81 so.)
   constexpr int CPR = DV / 8;     // 16-byte chunks per token row
   constexpr int RPI = 64 / CPR;   // token rows per store instruction
   const __amdgpu_buffer_rsrc_t grsrc =
-      make_rsrc(TOKGATE ? gtok + (size_t)fh * N * DV : Q, TOKGATE ? (uint32_t)N * DV * 2u : 0u);
+      make_rsrc(TOKGATE ? gtok + (size_t)fh * N * dvw : Q, TOKGATE ? (uint32_t)N * dvw * 2u : 0u);
   u32x4 gr[TOKGATE ? kQ : 1][TOKGATE ? 16 / RPI : 1];
   auto load_gate = [&](int ng, u32x4 (&gv)[TOKGATE ? 16 / RPI : 1]) {
     if constexpr (TOKGATE) {
 #pragma unroll
-      for (int r = 0; r < 16 / RPI; ++r)
+      for (int r = 0; r < 16 / RPI; ++r) {
+        const uint32_t off = ((uint32_t)(ng + r * RPI + lane / CPR) * dvw + lane % CPR * 8) * 2u;
         gv[r] = __builtin_bit_cast(
             u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                       grsrc, (int)(((uint32_t)(ng + r * RPI + lane / CPR) * DV + lane % CPR * 8) * 2u),
-                       0, 2));
+                       grsrc, (int)(!GENOUT || lane % CPR * 8 < dvw ? off : kOutOfRange), 0, 2));
+      }
     }
   };
   const __amdgpu_buffer_rsrc_t orsrc =
@@ -377,7 +381,7 @@ void readout_f32_kernel(const float* __restrict__ Q, const float* __restrict__ S
   lds_barrier();
 
   const __amdgpu_buffer_rsrc_t grsrc =
-      make_rsrc(TOKGATE ? gtok + (size_t)fh * N * DV : Q, TOKGATE ? (uint32_t)N * DV * 4u : 0u);
+      make_rsrc(TOKGATE ? gtok + (size_t)fh * N * dvo : Q, TOKGATE ? (uint32_t)N * dvo * 4u : 0u);
   const __amdgpu_buffer_rsrc_t orsrc =
       make_rsrc(obase, ((uint32_t)(N - 1) * ors + (uint32_t)dvo) * 4u);
   const floatx4* st4 = reinterpret_cast<const floatx4*>(st) + (li * SLD + 4 * lg) / 4;
@@ -438,8 +442,9 @@ void readout_f32_kernel(const float* __restrict__ Q, const float* __restrict__ S
       floatx4 y = acc[mb] * scale;
       const uint32_t ch = mb * 16 + 4 * lg;
       if constexpr (TOKGATE)
-        y *= __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                             grsrc, (int)(((uint32_t)n * DV + ch) * 4u), 0, 0));
+        y *= __builtin_bit_cast(
+            floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                         grsrc, (int)((int)ch < dvo ? ((uint32_t)n * dvo + ch) * 4u : kOutOfRange), 0, 0));
       // Channels past dvo (zero padding of a narrow head) are not stored.
       store_b128(orsrc, (int)ch < dvo ? ((uint32_t)n * ors + ch) * 4u : kOutOfRange,
                  __builtin_bit_cast(u32x4, y));

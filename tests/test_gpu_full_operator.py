@@ -427,3 +427,25 @@ def _token_major_np(y, clips, heads):
     _, F, N, d = y.shape
     return np.ascontiguousarray(
         y.reshape(clips, heads, F, N, d).transpose(0, 2, 3, 1, 4).reshape(clips, F, N, heads * d))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N", [1, 15, 17, 130])
+@pytest.mark.parametrize("dk,dv,heads", [(16, 16, 1), (16, 16, 2), (128, 16, 1), (16, 32, 2)])
+def test_narrow_token_gate(V, dtype, N, dk, dv, heads):
+    """The output gate per token of 16-channel heads is read as it is, rows
+    of the true width, in either output layout; NaN before and after it in
+    memory stays out of the result."""
+    import torch
+    w = I.custom("ex_narrow_gate", 1, 2, 3, N, dk, dv, dtype, seed=N + dk + dv)
+    x = I.make_inputs(w)
+    G = I.make_token_gates(w)
+    d = device_inputs(w, x)
+    g = to_device(G, dtype)
+    room = torch.full((g.numel() + 128,), float("nan"), dtype=g.dtype, device=g.device)
+    room[64:-64] = g.flatten()
+    y = V.forward(d["q"], d["k"], d["v"], d["beta"], None, gate_tokens=room[64:-64].view(g.shape), out_heads=heads)
+    exp = _oracle(w, x, G=G)
+    if heads > 1:
+        exp = exp.transpose(1, 2, 0, 3).reshape(1, w.F, N, 2 * dv)
+    assert rel_max_err(from_device(y), exp) <= tol_for(w)
