@@ -26,8 +26,8 @@
 // its L2) and every output is written once.  The work is bound by the fp32
 // FMAs (25 + 5 per output channel): 480 of ~690 vector instructions per wave
 // and frame for K, ~615 for V (counters), and two quarter-rate ones per
-// output.  At 16 heads x 36 frames x 48 x 80 tokens, d = 128, K takes 439 us
-// and V 397 in a trace (the two launches 2.8% faster than with ~760
+// output.  At 16 heads x 36 frames x 48 x 80 tokens, d = 128, K takes
+// 432 - 439 us and V 390 - 397 in a trace (the two launches 2.8% faster than with ~760
 // instructions: sums cleared instead of set by the first tap, addresses of
 // whole clips).  The filter on 4 x 4 x 4 matrix products with the taps in three
 // bf16 parts issues half the instructions and takes 491 and 413 us: the small
