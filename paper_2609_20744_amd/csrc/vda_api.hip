@@ -405,10 +405,11 @@ int check_forward(bool is_f32, const void* q, const void* k, const void* v, cons
   return VDA_OK;
 }
 
-// Lays out a checked forward call on device `dev`.
+// Lays out a checked forward call on device `dev` (split: frames may be split
+// into token ranges).
 void plan_forward(bool is_f32, const void* q, const void* k, const void* v, const float* beta,
                   const float* gate, int F, int N, int H, int d_k, int d_v,
-                  const vda_options& o, void* out, int dev, ForwardCall* c) {
+                  const vda_options& o, void* out, int dev, ForwardCall* c, bool split = true) {
   const size_t es = is_f32 ? 4 : 2;
   const size_t tok = (size_t)H * F * N;
   ForwardCall& C = *c;
@@ -424,7 +425,8 @@ void plan_forward(bool is_f32, const void* q, const void* k, const void* v, cons
   C.pk = pk, C.pv = pv;
   // The fp32 frozen rule's scan reads the statistics directly, so its frames
   // are not split; the bf16 frozen rule's map tiles sum the partials.
-  C.plan = C.frozen && is_f32 ? vda::SplitPlan{0, 1} : default_plan(dev, F, N, H, pk, pv, is_f32);
+  C.plan = !split || (C.frozen && is_f32) ? vda::SplitPlan{0, 1}
+                                          : default_plan(dev, F, N, H, pk, pv, is_f32);
   C.w = workspace_layout(F, H, pk, pv, C.plan);
   // With a chunked local window (bf16 storage, joint rule) the readout reads
   // the states at chunk boundaries only: chunk-wise scans compute just those,
@@ -582,19 +584,6 @@ char* scratch_ptr(int dev) {
   return ptrs[dev];
 }
 
-// Workspace bytes of vda_forward over `heads` heads starting at head h0.
-size_t group_workspace(const void* q, const void* k, const void* v, const float* beta,
-                       const float* gate, int F, int N, int h0, int heads, int d_k, int d_v,
-                       const vda_options& o, void* out, int dev) {
-  const size_t tokh = (size_t)F * N;  // tokens per head
-  ForwardCall C;
-  plan_forward(false, static_cast<const char*>(q) + h0 * tokh * d_k * 2,
-               static_cast<const char*>(k) + h0 * tokh * d_k * 2,
-               static_cast<const char*>(v) + h0 * tokh * d_v * 2, beta + h0 * tokh, gate + h0, F,
-               N, heads, d_k, d_v, o, static_cast<char*>(out) + h0 * tokh * d_v * 2, dev, &C);
-  return C.ws_bytes;
-}
-
 // vda_forward with its workspace in `scratch`: the heads run in consecutive
 // groups, each as one forward over its heads, as many heads per group as fit.
 int forward_noalloc_impl(const void* q, const void* k, const void* v, const float* beta,
@@ -608,34 +597,43 @@ int forward_noalloc_impl(const void* q, const void* k, const void* v, const floa
   char* base = scratch_ptr(dev);
   if (!base) return VDA_ERR_HIP;
   constexpr size_t cap = VDA_NOALLOC_SCRATCH_BYTES;
-  auto fits = [&](int h0, int n) {
-    return group_workspace(q, k, v, beta, gate, F, N, h0, n, d_k, d_v, o, out, dev) <= cap;
+  const size_t tokh = (size_t)F * N;  // tokens per head
+  // The forward over n heads from head h0 on, and whether it fits.  A single
+  // head that does not fit with its frames split runs with whole frames, so
+  // whether a call is accepted does not turn on the split plan's cost model.
+  auto plan_group = [&](int h0, int n, ForwardCall* C) {
+    for (const bool split : {true, false}) {
+      plan_forward(false, static_cast<const char*>(q) + h0 * tokh * d_k * 2,
+                   static_cast<const char*>(k) + h0 * tokh * d_k * 2,
+                   static_cast<const char*>(v) + h0 * tokh * d_v * 2, beta + h0 * tokh, gate + h0,
+                   F, N, n, d_k, d_v, o, static_cast<char*>(out) + h0 * tokh * d_v * 2, dev, C,
+                   split);
+      if (C->ws_bytes <= cap || n > 1) break;
+    }
+    return C->ws_bytes <= cap;
   };
+  ForwardCall C;
   // Nothing is enqueued unless every head fits on its own.
-  if (!fits(0, 1)) return VDA_ERR_SCRATCH;
+  if (!plan_group(0, 1, &C)) return VDA_ERR_SCRATCH;
   // Largest group size that fits, by bisection on the workspace of a group
   // at the first head (the workspace grows with the heads up to the
   // statistics' split partials; each group is re-checked below).
   int g = H;
-  if (!fits(0, H)) {
-    int lo = 1, hi = H;  // fits(lo), !fits(hi)
+  if (!plan_group(0, H, &C)) {
+    int lo = 1, hi = H;  // lo fits, hi does not
     while (hi - lo > 1) {
       const int mid = lo + (hi - lo) / 2;
-      if (fits(0, mid)) lo = mid;
+      if (plan_group(0, mid, &C)) lo = mid;
       else hi = mid;
     }
     g = lo;
   }
-  const size_t tokh = (size_t)F * N;
   for (int h0 = 0; h0 < H;) {
     int n = std::min(g, H - h0);
-    while (n > 1 && !fits(h0, n)) --n;
-    ForwardCall C;
-    plan_forward(false, static_cast<const char*>(q) + h0 * tokh * d_k * 2,
-                 static_cast<const char*>(k) + h0 * tokh * d_k * 2,
-                 static_cast<const char*>(v) + h0 * tokh * d_v * 2, beta + h0 * tokh, gate + h0,
-                 F, N, n, d_k, d_v, o, static_cast<char*>(out) + h0 * tokh * d_v * 2, dev, &C);
-    if (C.ws_bytes > cap) return VDA_ERR_SCRATCH;  // cannot happen: one head fits
+    while (!plan_group(h0, n, &C)) {
+      if (n == 1) return VDA_ERR_SCRATCH;  // cannot happen: one head fits
+      --n;
+    }
     if (launch_forward(C, base, stream) != hipSuccess) return VDA_ERR_HIP;
     h0 += n;
   }

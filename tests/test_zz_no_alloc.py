@@ -84,3 +84,28 @@ def test_noalloc_rejects_a_head_larger_than_the_array():
     assert not out.any()
     with pytest.raises(ValueError):
         V.forward_noalloc(d["q"], d["k"], d["v"], d["beta"], d["gate"], out=out)
+
+
+def test_noalloc_head_that_fits_with_whole_frames():
+    """A head whose partials of split frames would not fit the array runs with
+    its frames whole: whether it fits does not turn on the plan."""
+    import torch
+    from paper_2609_20744_amd import vda as V
+    F, N, dk, dv = 2288, 1023, 128, 32
+    tail, splits = V.default_split_plan(F, N, 1, dk, dv, is_f32=False)
+    states = 2 * F * dv * dk * 4
+    assert F * dk * (dk + dv) * 4 + states <= SCRATCH < (F + tail * (splits - 1)) * dk * (dk + dv) * 4 + states
+    print(f"noalloc at the array's edge: F={F} N={N} plan {tail} x {splits}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(46)
+    q, k, v = (torch.randn((1, F, N, d), generator=g, device="cuda") for d in (dk, dk, dv))
+    q, k = (torch.nn.functional.normalize(x, dim=-1).bfloat16() for x in (q, k))
+    v = v.bfloat16()
+    beta, gate = (torch.rand(s, generator=g, device="cuda") for s in ((1, F, N), (1,)))
+    ref = V.forward(q, k, v, beta, gate)
+    out = torch.full_like(ref, float("nan"))
+    st = _noalloc(V, {"q": q, "k": k, "v": v, "beta": beta, "gate": gate}, F, N, 1, dk, dv, out)
+    assert st == 0, V.status_string(st)
+    assert bool(torch.isfinite(out).all())
+    err = float((out.float() - ref.float()).abs().max() / ref.float().abs().max())
+    assert err <= TOL_BF16, err
