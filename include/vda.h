@@ -118,11 +118,12 @@ int vda_forward(const void* q, const void* k, const void* v,
  * the heads run in consecutive groups, each as one forward pass over its
  * heads (the largest groups that fit; a single head that fits only with its
  * frames unsplit runs so); head problems are independent, so the results are
- * vda_forward's up to the summation order of the split statistics.  Every call on a device shares that device's one array, and
- * the array keeps the last call's contents (nothing in it needs to start at
- * zero): calls that overlap in time on one device, on different streams or
- * from different threads, race and give undefined results; order them on
- * one stream or with events.
+ * vda_forward's up to the summation order of the split statistics.  Every
+ * call on a device shares that device's one array, and the array keeps the
+ * last call's contents (nothing in it needs to start at zero): calls that
+ * overlap in time on one device, on different streams or from different
+ * threads, race and give undefined results; order them on one stream or with
+ * events.
  * Errors: as vda_forward; VDA_ERR_SCRATCH (nothing enqueued) when a single
  * head's workspace is larger than the array even so, e.g. more than about 1000
  * frames at d_k = d_v = 128; VDA_ERR_HIP if the array's device address

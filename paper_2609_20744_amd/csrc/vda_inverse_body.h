@@ -39,10 +39,11 @@
 //
 // The 16 x 16 diagonal blocks are symmetric only to the rounding of A_t's own
 // operands: with bf16 storage beta * k is rounded to bf16 on one side of the
-// product, so A_t[i][j] and A_t[j][i] of one block differ by it.  The sweeps take D^{-1} as its own transpose, an unsymmetric
-// elimination would not; the two results differ by that rounding (bf16 passes
-// by about 1e-3 of the result), and are equally far from 64 bits (B_t Inv_t at
-// 1024 tokens of d_k = 128: 2.00e-3 and 2.00e-3; whole passes 3.1e-3 and 3.1e-3).
+// product, so A_t[i][j] and A_t[j][i] of one block differ by it.  The sweeps
+// take D^{-1} as its own transpose, an unsymmetric elimination would not; the
+// two results differ by that rounding (bf16 passes by about 1e-3 of the
+// result), and are equally far from 64 bits (B_t Inv_t at 1024 tokens of d_k =
+// 128: 2.00e-3 and 2.00e-3; whole passes 3.1e-3 and 3.1e-3).
 //
 // What bounds it (d_k = 128, shader-clock stamps, one matrix): the pivot
 // wave's chain, 8 x (1880 cycles of pivots, 117 each, + 700 for the next
