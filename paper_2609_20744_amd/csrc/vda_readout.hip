@@ -167,9 +167,15 @@ void readout_bf16_kernel(const uint16_t* __restrict__ Q, const float* __restrict
   };
   // TOKGATE: the output gate of the same groups, whole rows of the true dvw
   // channels in the stores' layout (rows past the frame and a padded head's
-  // channels read as zero); read once, so streamed (nt).  (From a copy padded
-  // to 32 channels, as the other inputs of 16-channel heads are, those heads
-  // took 100 us a pass at 12 heads x 40 frames x 1000 tokens, 81 so.)
+  // channels read as zero); read once, so streamed (nt), whatever its size: a
+  // gate still in the cache costs a little more so, one from memory less (us a
+  // pass, default -> nt, same buffers again / after a 400 MB fill: 8 MB of
+  // gates, 4 heads x 21 x 1560 x 32, 33.3 -> 34.4 and 43.8 -> 42.4; 34 MB, 8 x
+  // 16 x 1024 x 128, 82 -> 83 and 105 -> 98; 75 MB, 16 x 36 x 512 x 128, 101 ->
+  // 105 and 136 -> 121; 201 MB, 24 x 21 x 1560 x 128, 274 -> 268 and 318 ->
+  // 304).  (From a copy padded to 32 channels, as the other inputs of
+  // 16-channel heads are, those heads took 100 us a pass at 12 heads x 40
+  // frames x 1000 tokens, 81 so.)
   constexpr int CPR = DV / 8;     // 16-byte chunks per token row
   constexpr int RPI = 64 / CPR;   // token rows per store instruction
   const __amdgpu_buffer_rsrc_t grsrc =

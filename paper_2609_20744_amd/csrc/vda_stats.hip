@@ -529,7 +529,13 @@ int blocks_per_cu_t() {
 // kernel that wrote them, as in a model, nt is no better below 64 MB and
 // better above, where the same buffers used again soon no longer fit the
 // cache either (24 x 21 x 1560, 403 MB: 248 -> 228, the statistics alone 98 ->
-// 80).
+// 80).  Narrow heads, whose passes are mostly these reads, gain and lose the
+// most between (default -> nt; the second after ordinary stores to q, k, v):
+// 24 x 64 x 500 of 32 x 32, 98 MB   70 -> 78    85 -> 89    104 -> 94
+//  7 x 30 x 2000 of 64 x 64, 108 MB 69 -> 73    83 -> 89    106 -> 95
+// 16 x 64 x 1024 of 32 x 32, 134 MB 77 -> 85   103 -> 103   118 -> 109
+// 16 x 36 x 1024 of 64 x 64, 151 MB 96 -> 93   110 -> 109   140 -> 120
+//  1 x 300 x 2000 of 32 x 128, 192 MB 154 -> 162  183 -> 187  215 -> 192
 inline bool use_stream(long long kv_bytes) { return kv_bytes >= (64LL << 20); }
 
 template <int DK, int DV>
