@@ -94,3 +94,31 @@ def test_text_state_argument_errors(V):
     V.text_state(k, v, beta, out=out)
     torch.cuda.synchronize()
     assert torch.isfinite(out).all()
+
+
+# One token: S = w v k^T with w = beta / (1 + beta |k|^2) (Sherman-Morrison).  More row blocks than the product's grid
+# has workgroups, and more heads than one workgroup per row block could be launched for (2^32 threads).
+@pytest.mark.parametrize("H,dk,dv", [(8195, 32, 128), (16390, 64, 64), (8195, 128, 128), ((1 << 21) + 1, 32, 128)])
+def test_many_heads(V, H, dk, dv):
+    import torch
+    need = H * dk * (dk + 2 * dv) * 4 + H * (dk + dv) * 4
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < need + (16 << 30):
+        pytest.skip(f"{need >> 30} GiB of device memory needed")
+    print(f"text state H={H} d={dk}x{dv}, {need / 2**30:.1f} GiB", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H + dk)
+    k = torch.nn.functional.normalize(torch.randn((H, 1, dk), generator=g, device="cuda"), dim=-1)
+    v = torch.randn((H, 1, dv), generator=g, device="cuda")
+    beta = torch.rand((H, 1), generator=g, device="cuda")
+    S = V.text_state(k, v, beta)
+    err = 0.0
+    for h in range(0, H, 1 << 16):
+        s = slice(h, min(H, h + (1 << 16)))
+        w = beta[s] / (1.0 + beta[s] * k[s].square().sum(-1))
+        ref = (w[..., None] * v[s]).transpose(1, 2) * k[s]
+        err = max(err, float((S[s] - ref).abs().max() / ref.abs().max()))
+    del S
+    torch.cuda.empty_cache()
+    V.release_workspace()
+    assert err <= TOL_F32, err
